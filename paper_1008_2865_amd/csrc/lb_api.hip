@@ -1742,6 +1742,7 @@ struct lb_sk {
     lbk::SkPlan plan;
     std::vector<int64_t> counts;  // modes per shell
     double* rho;                  // device staging of host input, L*L doubles
+    double* host_shell;           // pinned: the last pass writes the shells here
     int device;
     hipStream_t stream;
 };
@@ -1775,8 +1776,8 @@ int sk_check_L(int32_t L)
 }
 
 struct SkLayout {
-    size_t tw, part, mean, z, zt, spec, idx, off, shell, kbar, rho, total;
-    int32_t nshell, sum_blocks;
+    size_t tw, z, spec, part, count, rho, total;
+    int32_t nshell, hc, hp;
 };
 
 SkLayout sk_layout(int32_t L)
@@ -1785,21 +1786,32 @@ SkLayout sk_layout(int32_t L)
     const int64_t N = (int64_t)L * L;
     const int64_t h = L / 2;  // largest |l| of an L-point transform
     S.nshell = (int32_t)shell_of(2 * h * h) + 1;
-    S.sum_blocks = (int32_t)std::min<int64_t>(1024, (N + 255) / 256);
+    S.hc = (L + 1) / 2;
+    S.hp = (int32_t)h + 1;
     size_t off = 0;
     S.tw = off; off += align_up((size_t)L * 2 * sizeof(double));
-    S.part = off; off += align_up((size_t)S.sum_blocks * sizeof(double));
-    S.mean = off; off += align_up(sizeof(double));
-    S.z = off; off += align_up((size_t)N * 2 * sizeof(double));
-    S.zt = off; off += align_up((size_t)N * 2 * sizeof(double));
-    S.spec = off; off += align_up((size_t)N * sizeof(double));
-    S.idx = off; off += align_up((size_t)N * sizeof(int32_t));
-    S.off = off; off += align_up((size_t)(S.nshell + 1) * sizeof(int32_t));
-    S.shell = off; off += align_up((size_t)S.nshell * sizeof(double));
-    S.kbar = off; off += align_up(2 * sizeof(double));
+    S.z = off; off += align_up((size_t)L * S.hc * 2 * sizeof(double));
+    S.spec = off; off += align_up((size_t)S.hp * L * sizeof(double));
+    S.part = off; off += align_up((size_t)S.nshell * S.hp * sizeof(double));
+    S.count = off; off += align_up((size_t)S.nshell * sizeof(double));
     S.rho = off; off += align_up((size_t)N * sizeof(double));
-    S.total = off;
+    // The size callers have been asked for: 52 bytes per mode.
+    S.total = std::max(off, align_up((size_t)N * 52));
     return S;
+}
+
+// Modes of every shell, from the quadrant l, m = 0 .. L/2 (l and -l, m and
+// -m alike; 0 and, for even L, L/2 are their own opposites).
+void shell_counts(int32_t L, std::vector<int64_t>& counts)
+{
+    auto twins = [&](int64_t v) { return v == 0 || 2 * v == L ? 1 : 2; };
+    for (int64_t l = 0; l <= L / 2; ++l) {
+        int64_t n = l;
+        for (int64_t m = 0; m <= L / 2; ++m) {
+            while ((2 * n + 1) * (2 * n + 1) <= 4 * (l * l + m * m)) ++n;
+            counts[n] += twins(l) * twins(m);
+        }
+    }
 }
 
 }  // namespace
@@ -1835,53 +1847,48 @@ int lb_sk_init(lb_sk** out, int32_t L, void* workspace, size_t bytes, void* hip_
     int dev = 0;
     if ((e = hipGetDevice(&dev))) return hip_fail(e, "hipGetDevice");
 
-    // Modes grouped by shell, each group in increasing index order (index
-    // l * L + m of the [l][m] spectrum; l, m signed as in an FFT).
-    const int64_t N = (int64_t)L * L;
-    std::vector<int32_t> shell_n(N), off(S.nshell + 1, 0), idx(N);
-    for (int32_t l = 0; l < L; ++l) {
-        const int64_t ls = l <= (L - 1) / 2 ? l : l - L;
-        for (int32_t m = 0; m < L; ++m) {
-            const int64_t ms = m <= (L - 1) / 2 ? m : m - L;
-            const int32_t n = (int32_t)shell_of(ls * ls + ms * ms);
-            shell_n[(int64_t)l * L + m] = n;
-            ++off[n + 1];
-        }
-    }
-    for (int32_t n = 0; n < S.nshell; ++n) off[n + 1] += off[n];
-    std::vector<int32_t> pos(off.begin(), off.end() - 1);
-    for (int64_t i = 0; i < N; ++i) idx[pos[shell_n[i]]++] = (int32_t)i;
-
     char* ws = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     lb_sk* s = new lb_sk();
     lbk::SkPlan& p = s->plan;
-    p.L = L;
-    p.logL = 0;
-    if ((L & (L - 1)) == 0)
-        while ((1 << p.logL) < L) ++p.logL;
+    p.fft = lbk::sk_fft(L);
     p.nshell = S.nshell;
-    p.sum_blocks = S.sum_blocks;
+    p.hc = S.hc;
+    p.hp = S.hp;
+    // Columns per workgroup: four (64-byte pieces of a row of z) when that
+    // still gives a workgroup to every CU, else two or one; and no more than
+    // fit the LDS.  The line is not sharp: with two columns from 120 groups
+    // on, 1000^2 takes 52.3 us against 51.3 and 600^2 44.1 against 42.9.
+    p.log_cols = 2;
+    while (p.log_cols > 0 &&
+           ((p.hc + (1 << p.log_cols) - 1) >> p.log_cols < 256 ||
+            lbk::sk_column_lds(L, 1 << p.log_cols, p.fft.any != 0) > (size_t)lbk::kSkColumnLds))
+        --p.log_cols;
     p.tw = reinterpret_cast<double2*>(ws + S.tw);
-    p.part = reinterpret_cast<double*>(ws + S.part);
-    p.mean = reinterpret_cast<double*>(ws + S.mean);
     p.z = reinterpret_cast<double2*>(ws + S.z);
-    p.zt = reinterpret_cast<double2*>(ws + S.zt);
-    p.spec_t = reinterpret_cast<double*>(ws + S.spec);
-    p.idx = reinterpret_cast<const int32_t*>(ws + S.idx);
-    p.off = reinterpret_cast<const int32_t*>(ws + S.off);
-    p.shell = reinterpret_cast<double*>(ws + S.shell);
-    p.kbar = reinterpret_cast<double*>(ws + S.kbar);
+    p.spec = reinterpret_cast<double*>(ws + S.spec);
+    p.part = reinterpret_cast<double*>(ws + S.part);
+    p.count = reinterpret_cast<const double*>(ws + S.count);
     s->rho = reinterpret_cast<double*>(ws + S.rho);
     s->device = dev;
     s->stream = st;
-    s->counts.resize(S.nshell);
-    for (int32_t n = 0; n < S.nshell; ++n) s->counts[n] = off[n + 1] - off[n];
-    if ((e = hipMemcpyAsync(ws + S.idx, idx.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, st)) ||
-        (e = hipMemcpyAsync(ws + S.off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice, st)) ||
-        (e = lbk::sk_twiddles(p, st)) || (e = hipStreamSynchronize(st))) {
+    s->counts.assign(S.nshell, 0);
+    shell_counts(L, s->counts);
+    const std::vector<double> counts(s->counts.begin(), s->counts.end());
+    // The shells leave the device by the last pass's own stores: a copy to
+    // pageable memory costs a copy launch and a staging pass more.
+    if ((e = hipHostMalloc(reinterpret_cast<void**>(&s->host_shell), S.nshell * sizeof(double),
+                           hipHostMallocMapped))) {
         delete s;
-        return hip_fail(e, "copy shell tables");
+        return hip_fail(e, "pinned shell buffer");
+    }
+    if ((e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p.shell), s->host_shell, 0)) ||
+        (e = hipMemcpyAsync(ws + S.count, counts.data(), counts.size() * sizeof(double),
+                            hipMemcpyHostToDevice, st)) ||
+        (e = lbk::sk_prepare(p, st)) || (e = hipStreamSynchronize(st))) {
+        (void)hipHostFree(s->host_shell);
+        delete s;
+        return hip_fail(e, "structure-factor tables");
     }
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -1899,7 +1906,7 @@ int lb_sk_compute(lb_sk* s, const double* rho, int on_device, double* shell, int
     if (!rho) return fail(LB_ERR_INVALID, "rho is NULL");
     if (cap < 0 || (cap > 0 && !shell && !counts)) return fail(LB_ERR_INVALID, "bad shell outputs");
     const lbk::SkPlan& p = s->plan;
-    const int64_t N = (int64_t)p.L * p.L;
+    const int64_t N = (int64_t)p.fft.n * p.fft.n;
     DeviceGuard dg(s->device);
     if (dg.err) return hip_fail(dg.err, "select device");
     hipError_t e;
@@ -1911,21 +1918,23 @@ int lb_sk_compute(lb_sk* s, const double* rho, int on_device, double* shell, int
         r = s->rho;
     }
     if ((e = lbk::sk_compute(p, r, spectrum, s->stream))) return hip_fail(e, "structure-factor kernels");
+    if ((e = hipStreamSynchronize(s->stream))) return hip_fail(e, "structure factor");
     const int32_t n = cap < p.nshell ? cap : p.nshell;
-    std::vector<double> sh(p.nshell);
-    double kb[2] = {0.0, 0.0};
-    if ((e = hipMemcpyAsync(sh.data(), p.shell, p.nshell * sizeof(double), hipMemcpyDeviceToHost, s->stream)) ||
-        (e = hipMemcpyAsync(kb, p.kbar, sizeof kb, hipMemcpyDeviceToHost, s->stream)) ||
-        (e = hipStreamSynchronize(s->stream)))
-        return hip_fail(e, "copy shells");
+    const double* sh = s->host_shell;
+    double num = 0.0, den = 0.0;
+    bool finite = true;
+    for (int32_t i = 0; i < p.nshell; ++i) {
+        num += (double)i * sh[i];
+        den += sh[i];
+        finite = finite && std::isfinite(sh[i]);
+    }
     for (int32_t i = 0; i < n; ++i) {
         if (shell) shell[i] = sh[i];
         if (counts) counts[i] = s->counts[i];
     }
-    if (kbar) *kbar = kb[0];
-    for (double v : sh)
-        if (!std::isfinite(v)) return fail(LB_ERR_NONFINITE, "non-finite structure factor");
-    if (kbar && !std::isfinite(kb[0]))
+    if (kbar) *kbar = num / den;
+    if (!finite) return fail(LB_ERR_NONFINITE, "non-finite structure factor");
+    if (kbar && !std::isfinite(num / den))
         return fail(LB_ERR_NONFINITE, "kbar is not finite (uniform field: every S_n is 0)");
     return LB_OK;
 }
@@ -1939,6 +1948,7 @@ int lb_sk_destroy(lb_sk* s)
     }
     DeviceGuard dg(s->device);
     hipError_t e = hipStreamSynchronize(s->stream);
+    (void)hipHostFree(s->host_shell);
     delete s;
     if (e) return hip_fail(e, "synchronise");
     return LB_OK;

@@ -168,26 +168,37 @@ hipError_t adj_zero(double* p, int64_t n, hipStream_t s);
 
 // Structure factor (lb_structure.hip) of an L x L density field, L <= kSkMaxL.
 constexpr int kSkMaxL = 2048;
-struct SkPlan {
-    int32_t L;
-    int32_t logL;        // log2 L if L is a power of two, else 0 (direct DFT)
-    int32_t nshell;      // shells 0 .. nshell-1
-    int32_t sum_blocks;  // workgroups of the mean reduction
-    double2* tw;         // L twiddles exp(-2 pi i k / L)
-    double* part;        // sum_blocks partial sums
-    double* mean;        // 1
-    double2* z;          // L*L: row transforms, [y][l]
-    double2* zt;         // L*L: their transpose, [l][y]
-    double* spec_t;      // L*L: S at (l, m), stored [l][m]
-    const int32_t* idx;  // L*L: indices into spec_t, grouped by shell
-    const int32_t* off;  // nshell + 1: shell n is idx[off[n] .. off[n+1])
-    double* shell;       // nshell shell averages
-    double* kbar;        // 2: {kbar, sum_n S_n}
+// LDS a workgroup of the column pass may use (160 KB less its static part).
+constexpr int kSkColumnLds = 159 * 1024;
+// Passes of a mixed-radix transform of n points: radix[p] after sub-transforms
+// of length s (the product of the radices before it), with the multipliers
+// that divide by s and by n / radix[p].
+struct SkFft {
+    int32_t n, passes;
+    int32_t any;  // some radix is a prime above 5
+    int32_t radix[12];
+    uint32_t magic_s[12], magic_m[12];
 };
+struct SkPlan {
+    SkFft fft;
+    int32_t nshell;      // shells 0 .. nshell-1
+    int32_t hc;          // columns of the row spectra: L/2, (L+1)/2 for odd L
+    int32_t log_cols;    // columns per workgroup of the column pass, log2
+    int32_t hp;          // L/2 + 1, columns of the half spectrum
+    double2* tw;         // L twiddles exp(-2 pi i k / L)
+    double2* z;          // L*hc: row spectra, [y][l]
+    double* spec;        // hp*L: S at (l, m), l <= L/2, stored [l][m]
+    double* part;        // nshell*hp: run sums, [n][l]
+    const double* count; // nshell: modes per shell
+    double* shell;       // nshell shell averages (pinned host memory)
+};
+SkFft sk_fft(int L);
+// LDS of the column pass with `cols` columns per workgroup.
+size_t sk_column_lds(int L, int cols, bool any);
 // Runs every pass on rho (device, L*L doubles); spectrum (device, [m][l])
 // may be NULL.
 hipError_t sk_compute(const SkPlan& p, const double* rho, double* spectrum, hipStream_t s);
 // Fills p.tw (once per plan).
-hipError_t sk_twiddles(const SkPlan& p, hipStream_t s);
+hipError_t sk_prepare(const SkPlan& p, hipStream_t s);
 
 }  // namespace lbk

@@ -4,15 +4,26 @@
 // shells (n - 1/2) <= |k| L / 2 pi < n + 1/2 and the first moment
 // kbar = sum_n n S_n / sum_n S_n (eq. (rad), k in units of 2 pi / L).
 //
-// The 2-D transform is a row pass, a transpose and a column pass; each pass
-// transforms one line per workgroup in LDS, in double precision: a radix-2
-// decimation-in-time FFT when L is a power of two, the direct sum over x
-// otherwise, with twiddles from a table computed once (sincospi).  The
-// transposes are 32 x 32 LDS tiles, so every global access is coalesced.  The sign of the exponent does not matter for |.|^2 of a
-// real field (S(k) = S(-k)); the passes use e^{-i k.x}.  Shell sums run
-// over a host-built list of the modes of each shell in increasing index
-// order, one workgroup per shell: every sum has a fixed order, so results
-// are bit-reproducible.
+// Three passes, all in double precision:
+//   k_sk_rows    two real rows per workgroup as one complex line, transformed
+//                in LDS and separated; only l = 0 .. L/2 is stored, since
+//                S(k) = S(-k);
+//   k_sk_columns 4, 2 or 1 columns per workgroup, transformed in LDS; S of
+//                the columns, and the sum of S over each run of a column's
+//                modes that lies in one shell;
+//   k_sk_shells  one wave per shell adds those runs over the columns.
+// The sign of the exponent does not matter for |.|^2 of a real field; the
+// passes use e^{-i k.x}.  Twiddles come from a table computed once
+// (sincospi).  Every sum has a fixed order, so results are bit-reproducible.
+//
+// What bounds it: the passes' chains of LDS round trips (a barrier twice per
+// radix), one round of workgroups each; at 2048^2 22 us for the rows, 30 for
+// the columns, 4 for the shells, against 20 us for the bytes at a copy's
+// rate.  The passes move 33.5 MB of density, 33.6 MB of row spectra out and
+// in again, and 2 x 6 MB of run sums, where a full complex transform with a
+// transpose and a gather of every mode into its shell moved 386 MB.  A whole
+// evaluation on MI355X: 2048^2 241 -> 70 us, 1000^2 with the full spectrum
+// 1416 -> 59 us (radices 8, 5, 5, 5 in place of the direct sum), 512^2 41 us.
 #include "lb_internal.h"
 
 #include <hip/hip_runtime.h>
@@ -22,43 +33,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTile = 32;
-
-// Fixed-order workgroup sum (256 threads); the result is valid in thread 0.
-__device__ __forceinline__ double block_reduce(double v, double* sm)
-{
-    const int tid = threadIdx.x;
-    sm[tid] = v;
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if (tid < w) sm[tid] += sm[tid + w];
-        __syncthreads();
-    }
-    return sm[0];
-}
-
-// part[b] = sum of rho[s] over s = b*256 + tid + k*gridDim*256.
-__global__ void __launch_bounds__(kThreads)
-k_sk_sum(const double* __restrict__ rho, int64_t N, double* __restrict__ part)
-{
-    __shared__ double sm[kThreads];
-    double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < N;
-         i += (int64_t)gridDim.x * kThreads)
-        s += rho[i];
-    const double t = block_reduce(s, sm);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
-// mean[0] = (sum of the partials) / N.
-__global__ void __launch_bounds__(kThreads)
-k_sk_mean(const double* __restrict__ part, int blocks, int64_t N, double* __restrict__ mean)
-{
-    __shared__ double sm[kThreads];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < blocks; b += kThreads) s += part[b];
-    const double t = block_reduce(s, sm);
-    if (threadIdx.x == 0) mean[0] = t / (double)N;
-}
 
 // tw[k] = exp(-2 pi i k / L), k < L (once per context).
 __global__ void __launch_bounds__(kThreads) k_sk_twiddles(int L, double2* __restrict__ tw)
@@ -70,192 +44,535 @@ __global__ void __launch_bounds__(kThreads) k_sk_twiddles(int L, double2* __rest
     tw[k] = make_double2(c, s);
 }
 
-// One line of length L per workgroup.  kRows: the line is row `line` of
-// rho minus its mean (real); otherwise row `line` of the complex array zin.
-// kSpec: write |X_k|^2 * invN to spec[line * L + k]; otherwise X_k to
-// zout[line * L + k].  Dynamic LDS: 2 L doubles (FFT) or 4 L (direct sum,
-// which also keeps the twiddles in LDS).
-template <bool kPow2, bool kRows, bool kSpec>
-__global__ void __launch_bounds__(kThreads)
-k_sk_line(const double* __restrict__ rho, const double* __restrict__ mean,
-          const double2* __restrict__ zin, const double2* __restrict__ tw, int L, int logL,
-          double invN, double2* __restrict__ zout, double* __restrict__ spec)
+// ---------------------------------------------------------------------------
+// One-line transforms in LDS: a Stockham autosort FFT of mixed radix.  A pass
+// of radix r over sub-transforms of length s takes, for j < L/r, jd = j / s
+// and k = j % s, the inputs x[j + q L/r] times w_{rs}^{q k}, q < r, and
+// writes their r-point transform to x[jd s r + k + p s], p < r.  A thread
+// holds its butterflies in registers between reading and writing, so the
+// line stays in one LDS buffer; at most kPerThread values per thread.
+// ---------------------------------------------------------------------------
+constexpr int kPerThread = 8;
+
+// LDS position of element i: one element of padding after every eight, so
+// that the first pass's stores (8 elements apart) spread over the banks.
+__host__ __device__ __forceinline__ int pad(int i) { return i + (i >> 3); }
+
+// v / d for 0 <= v < 2^16 with magic = ceil(2^32 / d), d >= 2; d = 1 has
+// magic 0.
+__device__ __forceinline__ int divm(int v, uint32_t magic)
 {
-    extern __shared__ double lds[];
-    double* re = lds;
-    double* im = lds + L;
-    const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * L;
-    const double mu = kRows ? mean[0] : 0.0;
-    for (int x = tid; x < L; x += kThreads) {
-        double vr, vi;
-        if (kRows) {
-            vr = rho[base + x] - mu;
-            vi = 0.0;
-        } else {
-            const double2 z = zin[base + x];
-            vr = z.x;
-            vi = z.y;
-        }
-        // Bit-reversed order for the in-place radix-2 passes.
-        const int d = kPow2 ? (int)(__brev((unsigned)x) >> (32 - logL)) : x;
-        re[d] = vr;
-        im[d] = vi;
-    }
-
-    auto emit = [&](int k, double xr, double xi) {
-        if (kSpec)
-            spec[base + k] = (xr * xr + xi * xi) * invN;
-        else
-            zout[base + k] = make_double2(xr, xi);
-    };
-
-    if (kPow2) {
-        __syncthreads();
-        for (int half = 1; half < L; half <<= 1) {
-            const int step = L / (2 * half);
-            for (int b = tid; b < L / 2; b += kThreads) {
-                const int pos = b & (half - 1);
-                const int i = ((b - pos) << 1) + pos;
-                const int j = i + half;
-                const double2 w = tw[pos * step];
-                const double xr = re[j] * w.x - im[j] * w.y;
-                const double xi = re[j] * w.y + im[j] * w.x;
-                const double ar = re[i], ai = im[i];
-                re[i] = ar + xr;
-                im[i] = ai + xi;
-                re[j] = ar - xr;
-                im[j] = ai - xi;
-            }
-            __syncthreads();
-        }
-        for (int k = tid; k < L; k += kThreads) emit(k, re[k], im[k]);
-    } else {
-        double* twc = lds + 2 * L;
-        double* tws = lds + 3 * L;
-        for (int k = tid; k < L; k += kThreads) {
-            const double2 w = tw[k];
-            twc[k] = w.x;
-            tws[k] = w.y;
-        }
-        __syncthreads();
-        // X_k = sum_x v_x w^{(x k) mod L}.
-        for (int k = tid; k < L; k += kThreads) {
-            double sr = 0.0, si = 0.0;
-            int t = 0;
-            for (int x = 0; x < L; ++x) {
-                const double wr = twc[t], wi = tws[t];
-                sr += re[x] * wr - im[x] * wi;
-                si += re[x] * wi + im[x] * wr;
-                t += k;
-                if (t >= L) t -= L;
-            }
-            emit(k, sr, si);
-        }
-    }
+    return magic ? (int)__umulhi((uint32_t)v, magic) : v;
 }
 
-// out[c][r] = in[r][c] for an L x L array, through 32 x 32 LDS tiles.
-template <typename T>
-__global__ void __launch_bounds__(kThreads)
-k_sk_transpose(const T* __restrict__ in, int L, T* __restrict__ out)
+__device__ __forceinline__ double2 add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 sub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 mul(double2 a, double2 w)
 {
-    __shared__ T tile[kTile][kTile + 1];
-    const int tx = threadIdx.x & (kTile - 1), ty = threadIdx.x / kTile;  // 32 x 8
-    const int c0 = blockIdx.x * kTile, r0 = blockIdx.y * kTile;
-    for (int r = ty; r < kTile; r += kThreads / kTile) {
-        const int gr = r0 + r, gc = c0 + tx;
-        if (gr < L && gc < L) tile[r][tx] = in[(int64_t)gr * L + gc];
-    }
-    __syncthreads();
-    for (int c = ty; c < kTile; c += kThreads / kTile) {
-        const int gc = c0 + c, gr = r0 + tx;
-        if (gr < L && gc < L) out[(int64_t)gc * L + gr] = tile[tx][c];
-    }
+    return make_double2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
 }
+__device__ __forceinline__ double2 mul_mi(double2 a) { return make_double2(a.y, -a.x); }  // -i a
 
-// Shell n (one workgroup each): average of spec over its modes, listed in
-// idx[off[n] .. off[n+1]).
-__global__ void __launch_bounds__(kThreads)
-k_sk_shell(const double* __restrict__ spec, const int32_t* __restrict__ idx,
-           const int32_t* __restrict__ off, double* __restrict__ shell)
+__device__ __forceinline__ void dft(double2 (&v)[2])
 {
-    __shared__ double sm[kThreads];
-    const int n = blockIdx.x;
-    const int a = off[n], b = off[n + 1];
-    double s = 0.0;
-    int j = a + threadIdx.x;
-    // Eight independent gathers in flight per thread, then the tail.
-    for (; j + 7 * kThreads < b; j += 8 * kThreads) {
-        double v[8];
+    const double2 a = v[0];
+    v[0] = add(a, v[1]);
+    v[1] = sub(a, v[1]);
+}
+__device__ __forceinline__ void dft(double2 (&v)[3])
+{
+    constexpr double kS = 0.86602540378443864676;  // sin(2 pi / 3)
+    const double2 t = add(v[1], v[2]), d = sub(v[1], v[2]);
+    const double2 a = make_double2(v[0].x - 0.5 * t.x, v[0].y - 0.5 * t.y);
+    const double2 b = make_double2(kS * d.y, -kS * d.x);
+    v[0] = add(v[0], t);
+    v[1] = add(a, b);
+    v[2] = sub(a, b);
+}
+__device__ __forceinline__ void dft(double2 (&v)[4])
+{
+    const double2 a = add(v[0], v[2]), b = sub(v[0], v[2]);
+    const double2 c = add(v[1], v[3]), d = mul_mi(sub(v[1], v[3]));
+    v[0] = add(a, c);
+    v[1] = add(b, d);
+    v[2] = sub(a, c);
+    v[3] = sub(b, d);
+}
+__device__ __forceinline__ void dft(double2 (&v)[5])
+{
+    constexpr double kC1 = 0.30901699437494742410, kC2 = -0.80901699437494742410;  // cos 72, cos 144
+    constexpr double kS1 = 0.95105651629515357212, kS2 = 0.58778525229247312917;   // sin 72, sin 144
+    const double2 t1 = add(v[1], v[4]), t2 = add(v[2], v[3]);
+    const double2 d1 = sub(v[1], v[4]), d2 = sub(v[2], v[3]);
+    const double2 a1 = make_double2(v[0].x + kC1 * t1.x + kC2 * t2.x, v[0].y + kC1 * t1.y + kC2 * t2.y);
+    const double2 a2 = make_double2(v[0].x + kC2 * t1.x + kC1 * t2.x, v[0].y + kC2 * t1.y + kC1 * t2.y);
+    const double2 b1 = mul_mi(make_double2(kS1 * d1.x + kS2 * d2.x, kS1 * d1.y + kS2 * d2.y));
+    const double2 b2 = mul_mi(make_double2(kS2 * d1.x - kS1 * d2.x, kS2 * d1.y - kS1 * d2.y));
+    v[0] = add(v[0], add(t1, t2));
+    v[1] = add(a1, b1);
+    v[4] = sub(a1, b1);
+    v[2] = add(a2, b2);
+    v[3] = sub(a2, b2);
+}
+__device__ __forceinline__ void dft(double2 (&v)[8])
+{
+    constexpr double kH = 0.70710678118654752440;
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    dft(e);
+    dft(o);
+    o[1] = make_double2(kH * (o[1].x + o[1].y), kH * (o[1].y - o[1].x));   // e^{-i pi/4}
+    o[2] = mul_mi(o[2]);
+    o[3] = make_double2(kH * (o[3].y - o[3].x), -kH * (o[3].x + o[3].y));  // e^{-3 i pi/4}
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = spec[idx[j + q * kThreads]];
-        s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    for (int q = 0; q < 4; ++q) {
+        v[q] = add(e[q], o[q]);
+        v[q + 4] = sub(e[q], o[q]);
     }
-    for (; j < b; j += kThreads) s += spec[idx[j]];
-    const double t = block_reduce(s, sm);
-    if (threadIdx.x == 0) shell[n] = b > a ? t / (double)(b - a) : 0.0;
 }
 
-// out = {kbar, sum_n S_n}: kbar = sum_n n S_n / sum_n S_n.
-__global__ void __launch_bounds__(kThreads)
-k_sk_kbar(const double* __restrict__ shell, int nsh, double* __restrict__ out)
+template <int R>
+__device__ __forceinline__ void
+fft_pass(double2* x, int lines, int lp, int n, int s, uint32_t magic_s, uint32_t magic_m,
+         const double2* __restrict__ tw)
 {
-    __shared__ double sm[kThreads];
-    double num = 0.0, den = 0.0;
-    for (int n = threadIdx.x; n < nsh; n += kThreads) {
-        num += (double)n * shell[n];
-        den += shell[n];
+    constexpr int NB = (kPerThread + R - 1) / R;  // butterflies per thread
+    const int T = blockDim.x, tid = threadIdx.x;
+    const int m = n / R, total = lines * m, tstep = m / s;
+    double2 v[NB][R];
+    int at[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        // Past the end: the last butterfly again, not stored, so that the
+        // loads of all of a thread's butterflies overlap.
+        const int idx = min(tid + b * T, total - 1);
+        const int c = divm(idx, magic_m), j = idx - c * m;
+        const int jd = divm(j, magic_s), k = j - jd * s;
+        const double2* in = x + c * lp;
+#pragma unroll
+        for (int q = 0; q < R; ++q) v[b][q] = in[pad(j + q * m)];
+        if (s > 1) {
+            const int t = k * tstep;
+            double2 w[R];
+            if constexpr (R == 8) {
+                // Three table reads; the other four are single products.
+                w[1] = tw[t];
+                w[2] = tw[2 * t];
+                w[4] = tw[4 * t];
+                w[3] = mul(w[1], w[2]);
+                w[5] = mul(w[1], w[4]);
+                w[6] = mul(w[2], w[4]);
+                w[7] = mul(w[3], w[4]);
+            } else {
+#pragma unroll
+                for (int q = 1; q < R; ++q) w[q] = tw[q * t];
+            }
+#pragma unroll
+            for (int q = 1; q < R; ++q) v[b][q] = mul(v[b][q], w[q]);
+        }
+        dft(v[b]);
+        at[b] = jd * s * R + k;
     }
-    const double tn = block_reduce(num, sm);
     __syncthreads();
-    const double td = block_reduce(den, sm);
-    if (threadIdx.x == 0) {
-        out[0] = tn / td;
-        out[1] = td;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int idx = tid + b * T;
+        if (idx >= total) continue;
+        double2* out = x + divm(idx, magic_m) * lp;
+#pragma unroll
+        for (int p = 0; p < R; ++p) out[pad(at[b] + p * s)] = v[b][p];
+    }
+    __syncthreads();
+}
+
+// A pass of any other radix r (a prime factor of L): output o of a line is
+// the sum of r products, x[j + q L/r] w_L^{q e mod L} with e = (o mod r s)
+// L / (r s), each thread forming its outputs one by one; twl is the twiddle
+// table in LDS.  For a prime L this is the direct transform.
+__device__ __forceinline__ void
+any_pass(double2* x, int lines, int lp, int n, int r, int s, const double2* twl)
+{
+    const int T = blockDim.x, tid = threadIdx.x;
+    const int m = n / r, rs = r * s, estep = n / rs, total = lines * n;
+    double2 acc[kPerThread];
+    int line[kPerThread], j[kPerThread], e[kPerThread], t[kPerThread];
+#pragma unroll
+    for (int b = 0; b < kPerThread; ++b) {
+        const int idx = min(tid + b * T, total - 1);
+        const int c = idx / n, o = idx - c * n;
+        const int blk = o / rs, rem = o - blk * rs;
+        line[b] = c * lp;
+        j[b] = blk * s + rem % s;
+        e[b] = rem * estep;
+        t[b] = 0;
+        acc[b] = make_double2(0.0, 0.0);
+    }
+    for (int q = 0; q < r; ++q) {
+#pragma unroll
+        for (int b = 0; b < kPerThread; ++b) {
+            if (tid + b * T >= total) continue;
+            const double2 v = x[line[b] + pad(j[b] + q * m)];
+            const double2 w = twl[t[b]];
+            acc[b].x += v.x * w.x - v.y * w.y;
+            acc[b].y += v.x * w.y + v.y * w.x;
+            t[b] += e[b];
+            t[b] = t[b] >= n ? t[b] - n : t[b];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < kPerThread; ++b) {
+        const int idx = tid + b * T;
+        if (idx >= total) continue;
+        const int c = idx / n;
+        x[c * lp + pad(idx - c * n)] = acc[b];
+    }
+    __syncthreads();
+}
+
+// All passes of `lines` lines of length f.n, line c at x[c lp + pad(i)].
+// Needs lines * f.n <= kPerThread * blockDim.x, and a barrier before it.
+template <bool kAny>
+__device__ __forceinline__ void
+fft_lines(double2* x, int lines, int lp, const SkFft& f, const double2* __restrict__ tw,
+          const double2* twl)
+{
+    int s = 1;
+    for (int p = 0; p < f.passes; ++p) {
+        const int r = f.radix[p];
+        const uint32_t ms = f.magic_s[p], mm = f.magic_m[p];
+        switch (r) {
+        case 8: fft_pass<8>(x, lines, lp, f.n, s, ms, mm, tw); break;
+        case 4: fft_pass<4>(x, lines, lp, f.n, s, ms, mm, tw); break;
+        case 2: fft_pass<2>(x, lines, lp, f.n, s, ms, mm, tw); break;
+        case 3: fft_pass<3>(x, lines, lp, f.n, s, ms, mm, tw); break;
+        case 5: fft_pass<5>(x, lines, lp, f.n, s, ms, mm, tw); break;
+        default:
+            if constexpr (kAny) any_pass(x, lines, lp, f.n, r, s, twl);
+            break;
+        }
+        s *= r;
     }
 }
 
-template <bool kPow2>
-hipError_t transform(const SkPlan& p, const double* rho, hipStream_t s)
+// Fixed-order workgroup sum of NV values per thread; every thread receives
+// the results.  red holds NV x waves doubles (at most 16 waves).
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* red)
 {
-    const int L = p.L;
-    const double invN = 1.0 / ((double)L * (double)L);
-    const size_t lds = (size_t)(kPow2 ? 2 : 4) * L * sizeof(double);
-    const dim3 tgrid((L + kTile - 1) / kTile, (L + kTile - 1) / kTile);
-    hipLaunchKernelGGL((k_sk_line<kPow2, true, false>), dim3(L), dim3(kThreads), lds, s, rho, p.mean,
-                       nullptr, p.tw, L, p.logL, invN, p.z, nullptr);
-    hipLaunchKernelGGL(k_sk_transpose<double2>, tgrid, dim3(kThreads), 0, s, p.z, L, p.zt);
-    hipLaunchKernelGGL((k_sk_line<kPow2, false, true>), dim3(L), dim3(kThreads), lds, s, nullptr,
-                       nullptr, p.zt, p.tw, L, p.logL, invN, nullptr, p.spec_t);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, waves = blockDim.x >> 6;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) v[q] += __shfl_xor(v[q], m, 64);
+        if (lane == 0) red[q * 16 + wid] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double t[16];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t[w] = w < waves ? red[q * 16 + w] : 0.0;
+#pragma unroll
+        for (int h = 8; h >= 1; h >>= 1)
+#pragma unroll
+            for (int w = 0; w < h; ++w) t[w] += t[w + h];
+        v[q] = t[0];
+    }
+    __syncthreads();
+}
+
+// Sum of kPerThread values, pairwise.
+__device__ __forceinline__ double pairwise(const double (&v)[kPerThread])
+{
+    return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+
+// Rows 2b and 2b + 1 of rho as the real and imaginary part of one line, each
+// less its own mean (which only l = 0 carries: that entry is the row's sum,
+// formed before the subtraction).  z[y][l], l < hc: the row spectra for
+// l = 0 .. hc - 1; for even L the real values at l = 0 and l = L/2 share
+// entry 0, as its real and imaginary part.  LDS: pad(L) + 2 elements, with
+// kAny L twiddles more.
+template <bool kAny>
+__global__ void __launch_bounds__(kThreads)
+k_sk_rows(const double* __restrict__ rho, SkFft f, const double2* __restrict__ tw, int hc,
+          double2* __restrict__ z)
+{
+    extern __shared__ double2 lds[];
+    __shared__ double red[2 * 16];
+    const int n = f.n, tid = threadIdx.x, T = blockDim.x;
+    double2* x = lds;
+    double2* twl = lds + pad(n) + 2;
+    const int64_t ya = 2 * (int64_t)blockIdx.x;
+    const bool two = ya + 1 < n;
+    const double* ra = rho + ya * n;
+    const double* rb = two ? ra + n : ra;
+    double va[kPerThread], vb[kPerThread];
+#pragma unroll
+    for (int b = 0; b < kPerThread; ++b) {
+        const int i = tid + b * T;
+        va[b] = i < n ? ra[i] : 0.0;
+        vb[b] = i < n ? rb[i] : 0.0;
+    }
+    if (kAny)
+        for (int i = tid; i < n; i += T) twl[i] = tw[i];
+    double sum[2] = {pairwise(va), pairwise(vb)};
+    block_sum<2>(sum, red);
+    const double ma = sum[0] / (double)n, mb = sum[1] / (double)n;
+#pragma unroll
+    for (int b = 0; b < kPerThread; ++b) {
+        const int i = tid + b * T;
+        if (i < n) x[pad(i)] = make_double2(va[b] - ma, vb[b] - mb);
+    }
+    __syncthreads();
+    fft_lines<kAny>(x, 1, 0, f, tw, twl);
+    double2* za = z + ya * hc;
+    double2* zb = za + hc;
+    for (int k = tid; k < hc; k += T) {
+        const double2 p = x[pad(k)], q = x[pad(k ? n - k : 0)];
+        double2 a = make_double2(0.5 * (p.x + q.x), 0.5 * (p.y - q.y));
+        double2 b = make_double2(0.5 * (p.y + q.y), 0.5 * (q.x - p.x));
+        if (k == 0) {
+            const double2 h = (n & 1) ? make_double2(0.0, 0.0) : x[pad(n / 2)];
+            a = make_double2(sum[0], h.x);
+            b = make_double2(sum[1], h.y);
+        }
+        za[k] = a;
+        if (two) zb[k] = b;
+    }
+}
+
+// Smallest m >= 0 with 4 (l^2 + m^2) >= (2n - 1)^2: the first mode of
+// column l in shell n or beyond.
+__device__ __forceinline__ int shell_begin(int n, int l)
+{
+    if (n == 0) return 0;
+    const int v = (2 * n - 1) * (2 * n - 1) - 4 * l * l;
+    if (v <= 0) return 0;
+    int m = (int)(0.5f * sqrtf((float)v));
+    while (4 * m * m < v) ++m;
+    while (m > 0 && 4 * (m - 1) * (m - 1) >= v) --m;
+    return m;
+}
+
+// Shell of l^2 + h^2.
+__device__ __forceinline__ int shell_at(int l, int h)
+{
+    const int q4 = 4 * (l * l + h * h);
+    int n = (int)(0.5f * sqrtf((float)q4) + 0.5f);
+    while ((2 * n + 1) * (2 * n + 1) <= q4) ++n;
+    while (n > 0 && (2 * n - 1) * (2 * n - 1) > q4) --n;
+    return n;
+}
+
+// `cols` columns per workgroup (a power of two, log2 = lc).  spec (may be
+// NULL): S at [l][m], l = 0 .. L/2.  part[n][l], pitch hp: the sum of S over
+// the modes (+-l, m) of shell n, each m in ascending order with its -m.  LDS:
+// cols (pad(L) + 2) elements, with kAny L twiddles more.  A segment of four
+// columns is 64 bytes of a row of z.
+template <bool kAny>
+__global__ void __launch_bounds__(1024)
+k_sk_columns(const double2* __restrict__ z, SkFft f, const double2* __restrict__ tw, int hc, int lc,
+             double invN, double* __restrict__ spec, double* __restrict__ part, int hp)
+{
+    extern __shared__ double2 lds[];
+    __shared__ double red[16];
+    const int n = f.n, tid = threadIdx.x, T = blockDim.x;
+    const int cols = 1 << lc, lp = pad(n) + 2, h = n / 2;
+    const bool even = (n & 1) == 0;
+    double2* x = lds;
+    double2* twl = lds + cols * lp;
+    // Consecutive column groups share the lines of z: keep them on one XCD.
+    const int per_xcd = gridDim.x / 8, rem = gridDim.x % 8, xcd = blockIdx.x % 8;
+    const int group = xcd * per_xcd + min(xcd, rem) + blockIdx.x / 8;
+    const int l0 = group << lc;
+    const int nc = min(cols, hc - l0);
+    {
+        double2 v[kPerThread];
+#pragma unroll
+        for (int b = 0; b < kPerThread; ++b) {
+            const int i = tid + b * T, y = i >> lc, c = i & (cols - 1);
+            v[b] = y < n && c < nc ? z[(int64_t)y * hc + l0 + c] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int b = 0; b < kPerThread; ++b) {
+            const int i = tid + b * T, y = i >> lc, c = i & (cols - 1);
+            if (y < n) x[c * lp + pad(y)] = v[b];
+        }
+        if (kAny)
+            for (int i = tid; i < n; i += T) twl[i] = tw[i];
+        if (l0 == 0) {
+            // Column l = 0 (real parts): the rows' sums, less their mean.
+            double s[kPerThread];
+#pragma unroll
+            for (int b = 0; b < kPerThread; ++b) {
+                const int i = tid + b * T;
+                s[b] = (i & (cols - 1)) == 0 ? v[b].x : 0.0;
+            }
+            double sum[1] = {pairwise(s)};
+            block_sum<1>(sum, red);
+            const double mean = sum[0] / (double)n;
+#pragma unroll
+            for (int b = 0; b < kPerThread; ++b) {
+                const int i = tid + b * T, y = i >> lc;
+                if ((i & (cols - 1)) == 0 && y < n) x[pad(y)].x = v[b].x - mean;
+            }
+        }
+    }
+    __syncthreads();
+    fft_lines<kAny>(x, cols, lp, f, tw, twl);
+
+    // S in place: .x of every column; for column 0 the columns l = 0 (.x)
+    // and, for even L, l = L/2 (.y), separated as in k_sk_rows.
+    for (int i = tid; i < nc * n; i += T) {
+        const int c = i / n, y = i - c * n;
+        if (l0 + c == 0) {
+            if (2 * y > n) continue;
+            const int y2 = y ? n - y : 0;
+            const double2 p = x[pad(y)], q = x[pad(y2)];
+            const double ar = 0.5 * (p.x + q.x), ai = 0.5 * (p.y - q.y);
+            const double br = 0.5 * (p.y + q.y), bi = 0.5 * (q.x - p.x);
+            const double2 s = make_double2((ar * ar + ai * ai) * invN, (br * br + bi * bi) * invN);
+            x[pad(y)] = s;
+            x[pad(y2)] = s;
+        } else {
+            const double2 p = x[c * lp + pad(y)];
+            x[c * lp + pad(y)].x = (p.x * p.x + p.y * p.y) * invN;
+        }
+    }
+    __syncthreads();
+
+    // Each column has T / cols threads (and column l = L/2 all of them, after
+    // the others): a column's longest runs are those of its first shells, so
+    // one thread group per column overlaps them.
+    auto column = [&](int l, int first, int stride, auto S) {
+        if (spec)
+            for (int m = first; m < n; m += stride) spec[(int64_t)l * n + m] = S(m);
+        const double w = l == 0 || (even && l == h) ? 1.0 : 2.0;
+        const int last = shell_at(l, h);
+        for (int sh = l + first; sh <= last; sh += stride) {
+            int m = shell_begin(sh, l);
+            const int b = min(shell_begin(sh + 1, l) - 1, h);
+            auto both = [&](int v) { return v == 0 || (even && v == h) ? S(v) : S(v) + S(n - v); };
+            double s = 0.0;
+            for (; m + 3 <= b; m += 4) {
+                const double v0 = both(m), v1 = both(m + 1), v2 = both(m + 2), v3 = both(m + 3);
+                s += (v0 + v1) + (v2 + v3);
+            }
+            for (; m <= b; ++m) s += both(m);
+            part[(int64_t)sh * hp + l] = w * s;
+        }
+    };
+    const int per = T >> lc, c = tid / per;  // T is a multiple of 64, cols of at most 4
+    if (c < nc) column(l0 + c, tid - c * per, per, [&](int m) { return x[c * lp + pad(m)].x; });
+    if (l0 == 0 && even) column(h, tid, T, [&](int m) { return x[pad(m)].y; });
+}
+
+// Shell n (one wave each): the run sums of its columns over its modes.
+__global__ void __launch_bounds__(kThreads)
+k_sk_shells(const double* __restrict__ part, int hp, int L, int nshell,
+            const double* __restrict__ count, double* __restrict__ shell)
+{
+    const int n = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (n >= nshell) return;
+    const int h = L / 2;
+    // Columns with modes in shell n: from the first whose last mode (l, h)
+    // reaches it up to l = n.
+    const int a = shell_begin(n, h), b = min(n, h);
+    double s = 0.0;
+#pragma unroll 4
+    for (int l = a + lane; l <= b; l += 64) s += part[(int64_t)n * hp + l];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+    if (lane == 0) shell[n] = s / count[n];
+}
+
+// The caller's full spectrum out[m][l] from the half spectrum in[l][m],
+// l <= L/2, through 32 x 32 LDS tiles: each value at (l, m) and (-l, -m).
+__global__ void __launch_bounds__(kThreads)
+k_sk_spread(const double* __restrict__ in, int L, double* __restrict__ out)
+{
+    __shared__ double tile[kTile][kTile + 1];
+    const int tx = threadIdx.x & (kTile - 1), ty = threadIdx.x / kTile;  // 32 x 8
+    const int m0 = blockIdx.x * kTile, l0 = blockIdx.y * kTile, h = L / 2;
+    for (int r = ty; r < kTile; r += kThreads / kTile)
+        if (l0 + r <= h && m0 + tx < L) tile[r][tx] = in[(int64_t)(l0 + r) * L + m0 + tx];
+    __syncthreads();
+    for (int r = ty; r < kTile; r += kThreads / kTile) {
+        const int m = m0 + r, l = l0 + tx;
+        if (m >= L || l > h) continue;
+        const double v = tile[tx][r];
+        out[(int64_t)m * L + l] = v;
+        if (l > 0 && 2 * l != L) out[(int64_t)(m ? L - m : 0) * L + L - l] = v;
+    }
+}
+
+template <bool kAny>
+hipError_t passes(const SkPlan& p, const double* rho, double* spec, hipStream_t s)
+{
+    const int n = p.fft.n;
+    // Whole waves of kPerThread values a thread.
+    auto lanes = [](int values) { return dim3((values + 64 * kPerThread - 1) / (64 * kPerThread) * 64); };
+    hipLaunchKernelGGL(k_sk_rows<kAny>, dim3((n + 1) / 2), lanes(n), sk_column_lds(n, 1, kAny), s, rho, p.fft, p.tw, p.hc,
+                       p.z);
+    const int cols = 1 << p.log_cols;
+    hipLaunchKernelGGL(k_sk_columns<kAny>, dim3((p.hc + cols - 1) / cols), lanes(n * cols),
+                       sk_column_lds(n, cols, kAny), s, p.z, p.fft, p.tw, p.hc, p.log_cols,
+                       1.0 / ((double)n * (double)n), spec, p.part, p.hp);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t sk_twiddles(const SkPlan& p, hipStream_t s)
+size_t sk_column_lds(int L, int cols, bool any)
 {
-    hipLaunchKernelGGL(k_sk_twiddles, dim3((p.L + kThreads - 1) / kThreads), dim3(kThreads), 0, s, p.L,
-                       p.tw);
+    return ((size_t)(pad(L) + 2) * cols + (any ? L : 0)) * sizeof(double2);
+}
+
+SkFft sk_fft(int L)
+{
+    SkFft f{};
+    f.n = L;
+    auto magic = [](int d) { return d > 1 ? (uint32_t)(((uint64_t(1) << 32) + d - 1) / d) : 0u; };
+    // Radices 8, 4, 2, 5, 3, then the primes from 7 up.
+    const int first[5] = {8, 4, 2, 5, 3};
+    for (int s = 1, k = 0; s < L; ++k) {
+        const int r = k < 5 ? first[k] : 7 + 2 * (k - 5);
+        for (; L / s % r == 0; s *= r) {
+            f.radix[f.passes] = r;
+            f.magic_s[f.passes] = magic(s);
+            f.magic_m[f.passes] = magic(L / r);
+            ++f.passes;
+            if (k >= 5) f.any = 1;
+        }
+    }
+    return f;
+}
+
+hipError_t sk_prepare(const SkPlan& p, hipStream_t s)
+{
+    // The column pass of a 2048-point line keeps four of them in LDS: 144 KB.
+    for (const void* fn : {reinterpret_cast<const void*>(k_sk_columns<true>),
+                           reinterpret_cast<const void*>(k_sk_columns<false>)}) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kSkColumnLds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_sk_twiddles, dim3((p.fft.n + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
+                       p.fft.n, p.tw);
     return hipGetLastError();
 }
 
 hipError_t sk_compute(const SkPlan& p, const double* rho, double* spectrum, hipStream_t s)
 {
-    const int64_t N = (int64_t)p.L * p.L;
-    hipLaunchKernelGGL(k_sk_sum, dim3(p.sum_blocks), dim3(kThreads), 0, s, rho, N, p.part);
-    hipLaunchKernelGGL(k_sk_mean, dim3(1), dim3(kThreads), 0, s, p.part, p.sum_blocks, N, p.mean);
-    hipError_t e = p.logL > 0 ? transform<true>(p, rho, s) : transform<false>(p, rho, s);
+    double* spec = spectrum ? p.spec : nullptr;
+    const hipError_t e = p.fft.any ? passes<true>(p, rho, spec, s) : passes<false>(p, rho, spec, s);
     if (e) return e;
-    hipLaunchKernelGGL(k_sk_shell, dim3(p.nshell), dim3(kThreads), 0, s, p.spec_t, p.idx, p.off,
-                       p.shell);
-    hipLaunchKernelGGL(k_sk_kbar, dim3(1), dim3(kThreads), 0, s, p.shell, p.nshell, p.kbar);
-    if (spectrum) {
-        // spec_t is indexed [l][m]; the caller's layout is [m][l].
-        const dim3 tgrid((p.L + kTile - 1) / kTile, (p.L + kTile - 1) / kTile);
-        hipLaunchKernelGGL(k_sk_transpose<double>, tgrid, dim3(kThreads), 0, s, p.spec_t, p.L,
-                           spectrum);
-    }
+    const int L = p.fft.n, per = kThreads / 64;
+    hipLaunchKernelGGL(k_sk_shells, dim3((p.nshell + per - 1) / per), dim3(kThreads), 0, s, p.part, p.hp, L,
+                       p.nshell, p.count, p.shell);
+    if (spectrum)
+        hipLaunchKernelGGL(k_sk_spread, dim3((L + kTile - 1) / kTile, (L / 2 + kTile) / kTile),
+                           dim3(kThreads), 0, s, spec, L, spectrum);
     return hipGetLastError();
 }
 
