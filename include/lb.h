@@ -80,7 +80,9 @@ typedef struct lb_params {
     int32_t tile_rows;   /* rows a workgroup updates per pipeline stage:
                             0 (library choice), 1 or 2                           */
     int32_t steps_per_launch; /* 0 (library choice: two per launch for LB_F32
-                            and LB_F16DEV on large lattices), 1, or 2: with 2
+                            and LB_F16DEV on large lattices; with the launch
+                            shape left to the library too, up to five per
+                            launch on other lattices), 1, or 2: with 2
                             the plain steps of LB_F32 and LB_F16DEV storage
                             between log points run two per launch (temporal
                             blocking); the fields are bit-identical to one
@@ -109,10 +111,10 @@ int lb_validate(const lb_params* p);
 int lb_launch_shape(const lb_params* p, int32_t* tile_x, int32_t* tile_y,
                     int32_t* tile_rows, int32_t* blocks);
 
-/* Shape of the two-step launches for these parameters (host only): lanes
- * per workgroup (each workgroup produces tile_x - 6 columns), rows per
- * workgroup and workgroups; all three are 0 when plain steps run one per
- * launch.  Any output may be NULL. */
+/* Shape of the two-step launches of the row-walking kernel for these
+ * parameters (host only): lanes per workgroup (each workgroup produces
+ * tile_x - 6 columns), rows per workgroup and workgroups; all three are 0
+ * when plain steps do not run in that kernel.  Any output may be NULL. */
 int lb_two_step_shape(const lb_params* p, int32_t* tile_x, int32_t* tile_y,
                       int32_t* blocks);
 

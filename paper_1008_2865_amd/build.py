@@ -11,6 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "liblb.so")
 SOURCES = [os.path.join(HERE, "csrc", "lb_kernels.hip"),
+           os.path.join(HERE, "csrc", "lb_tile.hip"),
            os.path.join(HERE, "csrc", "lb_adjoint.hip"),
            os.path.join(HERE, "csrc", "lb_structure.hip"),
            os.path.join(HERE, "csrc", "lb_noalloc.hip"),

@@ -259,17 +259,115 @@ Geom make_geom2(const lb_params& p, const Geom& g)
 }
 
 // Whether plain steps run two per launch: FP32 or half storage when asked
-// for (steps_per_launch = 2), and by default on lattices large enough for
-// tiles of 8 rows or more (below that the one-step kernel is as fast or
-// faster: FP32 1024^2 16.6 us/step either way, 512^2 11.7 against 7.7;
-// half storage 1024^2 18.1 against 15.5).  Half storage, two per launch
+// for (steps_per_launch = 2), and by default on lattices of 1.3 million sites
+// large enough for tiles of 8 rows or more (below that lb_tile.hip's kernel
+// is faster: FP32 1100^2 14.0 us/step against 15.9, half storage 14.2
+// against 17.0; 1200^2 16.3 against 15.8, 16.1 against 16.5).  Half storage, two per launch
 // against one: 2048^2 41.1 against 48.1 us/step, 4096^2 152.8 against
 // 166.3, 8192^2 551 against 627.
 bool use_two(const lb_params& p, const Geom& g2)
 {
     if (p.storage != LB_F32 && p.storage != LB_F16DEV) return false;
     if (p.steps_per_launch == 2) return true;
-    return p.steps_per_launch == 0 && g2.tile_y >= 8;
+    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (int64_t)p.nx * p.ny >= 1300000;
+}
+
+// Plain steps of several levels per launch (lb_tile.hip), for lattices that
+// do not run two per launch in the row walk.
+struct TilePlan {
+    lbk::TileGeom g;
+    int steps;       // most steps of a launch; 0: not used
+    bool single;     // also where one step is left
+};
+
+// The tile: about one per CU (256) while that keeps it within the region a
+// workgroup can hold, else a whole number of rounds of the workgroups that
+// are resident at once, so that no round runs partly empty.  Steps per launch
+// by the tile's area: the halo of a step costs three sites on every side, so
+// small tiles, whose time is the launch's, take more steps than large ones.
+// Measured us/step (tile, steps): FP32 64^2 4x4 5 steps 1.96, 4 2.04; 128^2
+// 8x8 4 2.19, 3 2.30; 256^2 16x16 3 2.53, 4 2.60; 448^2 28x28 3 3.82, 2
+// 4.20; 512^2 32x32 2 4.50, 24x24 3 5.16; 768^2 34x35 2 in two rounds' worth
+// 7.91, 24x24 in four 7.92; 1100^2 34x36 2 13.6, two per launch in the row
+// walk 15.9; 1200^2 16.3 against 15.8, 1300^2 18.1 against 17.2.
+// FP64 above about 1000^2 takes tiles of up to 24 x 26 and 256 threads, two
+// workgroups per CU, whose loads overlap each other's arithmetic: 1200^2 24x24
+// (4.9 rounds) 33.4 and 24x26 (4.6) 36.1 against 35.4 for 34x34 tiles, 2048^2
+// 98 against 111 (one step per launch 44 and 128).
+TilePlan make_tile(const lb_params& p, const Geom& g, bool two)
+{
+    TilePlan t{};
+    const int64_t N = (int64_t)p.nx * p.ny;
+    if (two || p.steps_per_launch != 0 || p.tile_x || p.tile_y || p.tile_rows ||
+        (uint64_t)g.plane * lbk::storage_bytes(p.storage) >= (uint64_t(1) << 32))
+        return t;
+    const bool f64 = p.storage == LB_F64, large = f64 && N > 1050000;
+    const bool round = N <= 256 * 34 * 36;  // one tile per CU
+    const int64_t slots = !large && (f64 || round) ? 256 : 512;
+    const int64_t area = (N + 255) / 256;
+    t.g.nx = p.nx;
+    t.g.ny = p.ny;
+    t.g.pitch = g.pitch;
+    t.g.plane = g.plane;
+    t.g.threads = large ? 256 : f64 || round ? 1024 : 512;
+    t.single = N <= 900000;
+    for (int k = area <= 24 ? 5 : area <= 112 ? 4 : large ? 2 : 3; k >= 1; --k) {
+        // Widest and tallest tile: within the region, and within one wrap
+        // of the lattice.
+        const int w = std::min(large ? 24 : lbk::kTilePitch - 6 * k + 2, p.nx - 3 * k + 2);
+        const int h = std::min(large ? 26 : lbk::kTileRows - 6 * k + 2, p.ny - 3 * k + 2);
+        if (w < 4 || h < 4) continue;
+        const int64_t fewest = (int64_t)((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
+        const int64_t tiles = (fewest + slots - 1) / slots * slots;
+        if (k == 3 && !large) {
+            // Three steps only where they need no more rounds than two.
+            const int w2 = lbk::kTilePitch - 10, h2 = lbk::kTileRows - 10;
+            const int64_t two_steps = (int64_t)((p.nx + w2 - 1) / w2) * ((p.ny + h2 - 1) / h2);
+            if (tiles > (two_steps + slots - 1) / slots * slots) continue;
+        }
+        // The smallest region among the splits into at most that many tiles.
+        int64_t best = 0;
+        for (int a = (p.nx + w - 1) / w; a <= tiles; ++a) {
+            const int tx = (p.nx + a - 1) / a;
+            const int64_t rows = tiles / a;
+            const int ty = std::max<int64_t>(4, (p.ny + rows - 1) / rows);
+            if (tx < 4 && a > (p.nx + w - 1) / w) break;
+            if (ty > h) break;
+            const int64_t region = (int64_t)(tx + 6 * k - 2) * (ty + 6 * k - 2);
+            if (best && region >= best) continue;
+            best = region;
+            t.steps = k;
+            t.g.tx = tx;
+            t.g.ty = ty;
+        }
+        if (!best) continue;
+        t.g.tiles_x = (p.nx + t.g.tx - 1) / t.g.tx;
+        t.g.tiles = t.g.tiles_x * ((p.ny + t.g.ty - 1) / t.g.ty);
+        return t;
+    }
+    return t;
+}
+
+// The tile geometry of a launch of `steps` <= t.steps steps.
+lbk::TileGeom tile_launch(const TilePlan& t, int steps)
+{
+    lbk::TileGeom g = t.g;
+    g.steps = steps;
+    for (int j = 0; j < steps; ++j) {
+        const uint32_t w = g.tx + 6 * (steps - 1 - j) + 4;
+        g.magic[j] = (uint32_t)(((uint64_t(1) << 32) + w - 1) / w);
+    }
+    return g;
+}
+
+// Steps of the next launch of a run of n plain steps: the run in as few
+// launches as t allows, evenly.  0: one step in the row walk.
+int tile_steps(const TilePlan& t, int64_t n)
+{
+    if (!t.steps || n < 1) return 0;
+    const int64_t launches = (n + t.steps - 1) / t.steps;
+    const int k = (int)((n + launches - 1) / launches);
+    return k > 1 || t.single ? k : 0;
 }
 
 // Workspace layout, each region 256-byte aligned.
@@ -299,6 +397,7 @@ struct lb_ctx {
     Geom g;
     Geom g2;     // two-step launches: tile_x lanes make tile_x - 6 columns
     bool two;    // plain steps run two per launch where they can
+    TilePlan tile;  // else several per launch on tiles, where that is faster
     Coef coef;
     int device;
     hipStream_t stream;
@@ -502,6 +601,7 @@ int lb_init(lb_ctx** out, const lb_params* p, void* workspace, size_t bytes,
     c->g = g;
     c->g2 = make_geom2(*p, g);
     c->two = use_two(*p, c->g2);
+    c->tile = make_tile(*p, g, c->two);
     c->coef = make_coef(*p);
     c->device = dev;
     c->stream = st;
@@ -574,6 +674,20 @@ int lb_step(lb_ctx* c, int64_t n)
         const void* src = c->buf[c->cur];
         void* dst = c->buf[c->cur ^ 1];
         const bool log = le > 0 && c->t % le == 0 && c->last_logged != c->t;
+        if (!log && c->tile.steps) {
+            int64_t run = n - s;  // plain steps up to the next logged one
+            if (le > 0) run = std::min(run, le - c->t % le);
+            if (const int k = tile_steps(c->tile, run)) {
+                c->coef.step = (uint32_t)c->t;
+                hipError_t e = lbk::launch_tile(c->p.storage, src, dst, tile_launch(c->tile, k), c->coef, nullptr,
+                                                c->stream);
+                if (e) return hip_fail(e, "tile kernel launch");
+                c->cur ^= 1;
+                c->t += k;
+                s += k - 1;
+                continue;
+            }
+        }
         // Two plain steps in one launch when neither state is logged.
         if (c->two && !log && s + 1 < n && !(le > 0 && (c->t + 1) % le == 0)) {
             c->coef.step = (uint32_t)c->t;

@@ -109,6 +109,22 @@ hipError_t launch_step2_batch(int storage, int tile_x, const BatchLattice* desc,
 // kernel's registers and LDS, per compute unit, times the compute units.
 // -1 when no device can be asked.
 int step2_resident(int storage, int tile_x);
+// Several plain steps in one launch (lb_tile.hip): tiles of tx x ty sites,
+// whose region of the first step, tx + 6 steps - 2 by ty + 6 steps - 2
+// sites, fits kTilePitch x kTileRows and wraps around the lattice at most
+// once.  A population plane spans less than 2^32 bytes.  With a tape (F64 and
+// F32 only), step j also writes the tape entry of the state it leaves to
+// tape + 4 j nx ny.
+constexpr int kTilePitch = 44, kTileRows = 46, kTileMaxSteps = 5;
+struct TileGeom {
+    int32_t nx, ny, pitch;
+    int64_t plane;
+    int32_t tx, ty, tiles_x, tiles, threads;
+    int32_t steps;                  // of this launch
+    uint32_t magic[kTileMaxSteps];  // division by the region's width, by step
+};
+hipError_t launch_tile(int storage, const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape,
+                       hipStream_t s);
 hipError_t launch_final(const double* partials, int blocks, double t,
                         double half_A1, double* out_row, hipStream_t s);
 hipError_t launch_step_batch(int storage, int mode, int tile_x, int rows_per_iter, int min_tile_y,

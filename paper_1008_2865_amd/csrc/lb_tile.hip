@@ -1,0 +1,202 @@
+// Several time steps of a small lattice in one launch.
+//
+// A workgroup owns tx x ty sites and advances them `steps` time levels on
+// chip.  It pulls the populations of its tile with a halo of 3 steps - 1
+// sites from memory, and each step then consumes three sites of halo (two
+// for the psi stencil, one for the streaming).  Per step:
+//   the densities' psi of every site in reach into LDS | barrier | force and
+//   collision of the sites two in from the edge, their post-collision
+//   populations into LDS (the last step: to memory) | barrier.
+// A thread holds the populations of its sites in registers between the two
+// halves, so the LDS planes are overwritten in place.  Every site goes
+// through the psi_of, density and site_collide of the one-step kernel, and
+// half storage rounds into LDS as a store to memory would, so the fields are
+// the same bits for any tile and any number of steps per launch.
+//
+// What bounds it: on small lattices the launch and the latency of its loads
+// (about 4 us, which the steps of a launch share) and the issue of the halo's
+// arithmetic, about 1.2 us a step in single and 2 us in double precision; on
+// lattices of several tiles per CU the arithmetic, 180 (255) vector
+// instructions per site and step, 1.2 to 1.4 times the sites for the halo.  A
+// row walk of one step per launch spends 4.6 to 7 us on any small lattice.
+// us/step before and after: FP32 64^2 4.4 -> 2.0, 256^2 5.6 -> 2.5, 512^2
+// 7.5 -> 4.5, 997x701 12.8 -> 9.4; FP64 64^2 6.4 -> 2.7, 512^2 13.5 -> 7.2,
+// 1200^2 44 -> 33, 2048^2 128 -> 98.
+#include "lb_site.h"
+
+namespace lbk {
+namespace {
+
+// base[e] for an element offset whose byte offset fits 32 bits: a uniform base
+// plus a 32-bit lane offset needs no 64-bit address arithmetic per load.
+template <typename T>
+__device__ __forceinline__ const T* at32(const T* base, int e)
+{
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)e * (uint32_t)sizeof(T));
+}
+
+template <class P, int NT, int kPitch, int kRows, bool kTape>
+__global__ void __launch_bounds__(NT)
+k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, TileGeom g,
+       CoefT<typename P::C> k, typename P::C* __restrict__ tape)
+{
+    using S = typename P::S;
+    using C = typename P::C;
+    constexpr int R = (kPitch * kRows + NT - 1) / NT;  // sites per thread
+    constexpr int kPostPitch = kPitch - 4;             // post-collision planes: 2 sites in
+    constexpr int kPostPlane = kPostPitch * (kRows - 4);
+    extern __shared__ double lds[];
+    C* const psi = reinterpret_cast<C*>(lds);
+    S* const post = reinterpret_cast<S*>(psi + kPitch * kRows);
+
+    const int tid = threadIdx.x;
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);
+    const int sy = lb / g.tiles_x;
+    const int x0 = (lb - sy * g.tiles_x) * g.tx, y0 = sy * g.ty;
+    const int nx = g.nx, ny = g.ny;
+    const Offs<P> o(k.rho_ref);
+    const S* pl[9];
+    S* pd[9];
+    S* lp[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        pl[i] = src + (int64_t)i * g.plane;
+        pd[i] = dst + (int64_t)i * g.plane;
+        lp[i] = post + i * kPostPlane;
+    }
+
+#pragma unroll 1
+    for (int j = 0; j < g.steps; ++j) {
+        // Sites in reach of this step: the tile and `halo` more on each side,
+        // 3 j in from the first step's region.
+        const int halo = 3 * (g.steps - 1 - j) + 2, in = 3 * j;
+        const int w = g.tx + 2 * halo, h = g.ty + 2 * halo, ns = w * h;
+        const uint32_t magic = g.magic[j];
+        // Site i of this thread; past the end the last site again (the same
+        // values written twice), so that no load is conditional.
+        auto site = [&](int i, int& x, int& y) {
+            const int s = min(tid + i * NT, ns - 1);
+            y = (int)__umulhi((uint32_t)s, magic);
+            x = s - y * w;
+        };
+        C F[R][9];
+        if (j == 0) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if (i * NT >= ns) break;
+                int x, y;
+                site(i, x, y);
+                const int gx = wrapi(x0 - halo + x, nx), gy = wrapi(y0 - halo + y, ny);
+                const int xs[3] = {gx == nx - 1 ? 0 : gx + 1, gx, gx == 0 ? nx - 1 : gx - 1};
+                const int r = gy * g.pitch;
+                const int ys[3] = {gy == ny - 1 ? 0 : r + g.pitch, r, gy == 0 ? (ny - 1) * g.pitch : r - g.pitch};
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+                    F[i][q] = o.ld(at32(pl[q], ys[1 + kQCy[q]] + xs[1 + kQCx[q]]), o.of(q));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if (i * NT >= ns) break;
+                int x, y;
+                site(i, x, y);
+                const int at = (y + in - 2) * kPostPitch + x + in - 2;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) F[i][q] = o.ld(lp[q] + at - kQCy[q] * kPostPitch - kQCx[q], o.of(q));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (i * NT >= ns) break;
+            int x, y;
+            site(i, x, y);
+            psi[(y + in) * kPitch + x + in] = psi_of(density(F[i]), k);
+        }
+        __syncthreads();
+
+        const bool last = j + 1 == g.steps;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (i * NT >= ns) break;
+            int x, y;
+            site(i, x, y);
+            if (tid + i * NT >= ns || x < 2 || x >= w - 2 || y < 2 || y >= h - 2) continue;
+            const int c = (y + in) * kPitch + x + in;
+            const Stencil<C> st(psi - 2 * kPitch, psi - kPitch, psi, psi + kPitch, psi + 2 * kPitch, c);
+            C q[9], tp[4];
+            site_collide<kTape, P::kDev>(F[i], st, k, q, tp, o.o1, o.o2);
+            const int ux = x0 - halo + x, uy = y0 - halo + y;  // before the periodic wrap
+            const bool own = ux >= x0 && ux < min(x0 + g.tx, nx) && uy >= y0 && uy < min(y0 + g.ty, ny);
+            const uint32_t rnd = P::kDev ? site_hash(wrapi(ux, nx), wrapi(uy, ny), k.step + j) : 0u;
+            if (!last)
+                store_site<P>(lp, (y + in - 2) * kPostPitch + x + in - 2, q, o, rnd);
+            else if (own)
+                store_site<P>(pd, uy * g.pitch + ux, q, o, rnd);
+            if (kTape && own) {
+                const int64_t N = (int64_t)nx * ny, at = (int64_t)uy * nx + ux;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tape[(4 * j + v) * N + at] = tp[v];
+            }
+        }
+        if (!last) __syncthreads();
+    }
+}
+
+template <class P, int NT, int kPitch, int kRows>
+hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
+{
+    using S = typename P::S;
+    using C = typename P::C;
+    const auto k = convert<C>(c);
+    const S* a = static_cast<const S*>(src);
+    S* b = static_cast<S*>(dst);
+    constexpr size_t psi = sizeof(C) * kPitch * kRows, post = sizeof(S) * 9 * (kPitch - 4) * (kRows - 4);
+    const size_t lds = psi + (g.steps > 1 ? post : 0);
+    if (tape) {
+        if constexpr (P::kDev)
+            return hipErrorInvalidValue;
+        else
+            hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, true>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
+                               static_cast<C*>(tape));
+    } else {
+        hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, false>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
+                           static_cast<C*>(nullptr));
+    }
+    return hipGetLastError();
+}
+
+template <class P>
+hipError_t tile_p(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
+{
+    const int w = g.tx + 6 * g.steps - 2, h = g.ty + 6 * g.steps - 2;
+    if (g.steps < 1 || g.steps > kTileMaxSteps || w > kTilePitch || h > kTileRows) return hipErrorInvalidValue;
+    // The first step's region: 34 x 36 sites keep two double-precision
+    // workgroups on a CU, 44 x 46 one.
+    const bool small = w <= 34 && h <= 36;
+    switch (g.threads) {
+    case 1024: return small ? tile_nt<P, 1024, 34, 36>(src, dst, g, c, tape, s)
+                            : tile_nt<P, 1024, kTilePitch, kTileRows>(src, dst, g, c, tape, s);
+    case 512: return small ? tile_nt<P, 512, 34, 36>(src, dst, g, c, tape, s)
+                           : tile_nt<P, 512, kTilePitch, kTileRows>(src, dst, g, c, tape, s);
+    case 256:
+        if constexpr (sizeof(typename P::C) == 8)
+            if (small) return tile_nt<P, 256, 34, 36>(src, dst, g, c, tape, s);
+        return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_tile(int storage, const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape,
+                       hipStream_t s)
+{
+    switch (storage) {
+    case ST_F64: return tile_p<PF64>(src, dst, g, c, tape, s);
+    case ST_F32: return tile_p<PF32>(src, dst, g, c, tape, s);
+    case ST_F16DEV: return tile_p<PF16>(src, dst, g, c, tape, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace lbk
