@@ -272,6 +272,41 @@ bool use_two(const lb_params& p, const Geom& g2)
     return p.steps_per_launch == 0 && g2.tile_y >= 8 && (int64_t)p.nx * p.ny >= 1300000;
 }
 
+// Tiles of at most w x h sites that cover an nx x ny lattice, rounded up to
+// whole rounds of `slots` resident workgroups.
+int64_t round_tiles(int nx, int ny, int w, int h, int64_t slots)
+{
+    const int64_t fewest = (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h);
+    return (fewest + slots - 1) / slots * slots;
+}
+
+struct TileSplit {
+    int tx, ty;
+};
+
+// The split into at most round_tiles tiles of at most w x h (and, unless the
+// lattice itself is narrower, at least `least`) sites whose region, `halo`
+// sites larger in both directions, is smallest.
+TileSplit split_tiles(int nx, int ny, int w, int h, int least, int64_t slots, int halo)
+{
+    TileSplit s{};
+    const int64_t tiles = round_tiles(nx, ny, w, h, slots);
+    const int first = (nx + w - 1) / w;
+    int64_t best = 0;
+    for (int a = first; a <= tiles; ++a) {
+        const int tx = (nx + a - 1) / a;
+        if (tx < least && a > first) break;
+        const int64_t rows = tiles / a;
+        const int ty = (int)std::max<int64_t>(std::min(least, h), (ny + rows - 1) / rows);
+        if (ty > h) break;
+        const int64_t region = (int64_t)(tx + halo) * (ty + halo);
+        if (best && region >= best) continue;
+        best = region;
+        s = TileSplit{tx, ty};
+    }
+    return s;
+}
+
 // Plain steps of several levels per launch (lb_tile.hip), for lattices that
 // do not run two per launch in the row walk.
 struct TilePlan {
@@ -317,30 +352,15 @@ TilePlan make_tile(const lb_params& p, const Geom& g, bool two)
         const int w = std::min(large ? 24 : lbk::kTilePitch - 6 * k + 2, p.nx - 3 * k + 2);
         const int h = std::min(large ? 26 : lbk::kTileRows - 6 * k + 2, p.ny - 3 * k + 2);
         if (w < 4 || h < 4) continue;
-        const int64_t fewest = (int64_t)((p.nx + w - 1) / w) * ((p.ny + h - 1) / h);
-        const int64_t tiles = (fewest + slots - 1) / slots * slots;
-        if (k == 3 && !large) {
-            // Three steps only where they need no more rounds than two.
-            const int w2 = lbk::kTilePitch - 10, h2 = lbk::kTileRows - 10;
-            const int64_t two_steps = (int64_t)((p.nx + w2 - 1) / w2) * ((p.ny + h2 - 1) / h2);
-            if (tiles > (two_steps + slots - 1) / slots * slots) continue;
-        }
-        // The smallest region among the splits into at most that many tiles.
-        int64_t best = 0;
-        for (int a = (p.nx + w - 1) / w; a <= tiles; ++a) {
-            const int tx = (p.nx + a - 1) / a;
-            const int64_t rows = tiles / a;
-            const int ty = std::max<int64_t>(4, (p.ny + rows - 1) / rows);
-            if (tx < 4 && a > (p.nx + w - 1) / w) break;
-            if (ty > h) break;
-            const int64_t region = (int64_t)(tx + 6 * k - 2) * (ty + 6 * k - 2);
-            if (best && region >= best) continue;
-            best = region;
-            t.steps = k;
-            t.g.tx = tx;
-            t.g.ty = ty;
-        }
-        if (!best) continue;
+        if (k == 3 && !large &&
+            round_tiles(p.nx, p.ny, w, h, slots) >
+                round_tiles(p.nx, p.ny, lbk::kTilePitch - 10, lbk::kTileRows - 10, slots))
+            continue;  // three steps only where they need no more rounds than two
+        const TileSplit s = split_tiles(p.nx, p.ny, w, h, 4, slots, 6 * k - 2);
+        if (!s.tx) continue;
+        t.steps = k;
+        t.g.tx = s.tx;
+        t.g.ty = s.ty;
         t.g.tiles_x = (p.nx + t.g.tx - 1) / t.g.tx;
         t.g.tiles = t.g.tiles_x * ((p.ny + t.g.ty - 1) / t.g.ty);
         return t;
@@ -360,13 +380,20 @@ lbk::TileGeom tile_launch(const TilePlan& t, int steps)
     return g;
 }
 
-// Steps of the next launch of a run of n plain steps: the run in as few
-// launches as t allows, evenly.  0: one step in the row walk.
+// Steps of the next launch of a run of n: as few launches as `most` steps
+// each allow, evenly.
+int even_steps(int64_t n, int most)
+{
+    const int64_t launches = (n + most - 1) / most;
+    return (int)((n + launches - 1) / launches);
+}
+
+// Steps of the next launch of a run of n plain steps on tiles; 0: one step in
+// the row walk.
 int tile_steps(const TilePlan& t, int64_t n)
 {
     if (!t.steps || n < 1) return 0;
-    const int64_t launches = (n + t.steps - 1) / t.steps;
-    const int k = (int)((n + launches - 1) / launches);
+    const int k = even_steps(n, t.steps);
     return k > 1 || t.single ? k : 0;
 }
 
@@ -1375,6 +1402,66 @@ int lb_batch_destroy(lb_batch* b)
 // ---------------------------------------------------------------------------
 // Adjoint of a run: gradients of L = (E(T) - E*)^2 + beta A(T).
 // ---------------------------------------------------------------------------
+namespace {
+
+// Tiles of the adjoint steps, and the most steps of a launch.
+struct AdjPlan {
+    lbk::AdjTile g;
+    int steps;
+};
+
+// About one tile per CU, as for the plain steps (make_tile), then whole rounds
+// of the workgroups resident at once.  A step's halo is two sites wider than a
+// plain step's, so launches take three steps up to 16 x 16 tiles and two
+// beyond.  Double precision keeps 512 threads, whose registers hold a site's
+// adjoint without spilling.  Measured us/step, backward pass of a run in one
+// segment: FP32 96x80 6x5 tiles 3 steps 4.8, 4 4.9; 256^2 16x16 3 5.9, 2 6.1;
+// 512^2 32x32 2 8.2, 1 10.7, 24x24 3 12.1, 32x16 2 8.8; 1024^2 32x32 2 with
+// 512 threads 28.6, with 1024 33.3; FP64 96x80 6x5 3 5.8, 2 6.0; 256^2 16x16 2
+// 7.0, 3 7.4; 512^2 32x32 2 12.8.
+AdjPlan adj_plan(int nx, int ny, bool f64)
+{
+    AdjPlan t{};
+    const int64_t N = (int64_t)nx * ny, area = (N + 255) / 256;
+    const bool round = area <= lbk::kAdjTileMax * lbk::kAdjTileMax;
+    const int64_t slots = f64 || round ? 256 : 512;
+    t.g.threads = f64 || !round ? 512 : 1024;
+    for (int k = area <= (f64 ? 144 : 256) ? 3 : 2; k >= 1; --k) {
+        const int top = k == 3 ? 24 : lbk::kAdjTileMax;  // the halo fits a second round of the threads
+        const int w = std::min(top, nx - 3 * k), h = std::min(top, ny - 3 * k);
+        if (w < 2 || h < 2) continue;
+        const TileSplit s = split_tiles(nx, ny, w, h, 4, slots, 6 * k + 2);
+        if (!s.tx) continue;
+        t.steps = k;
+        t.g.tx = s.tx;
+        t.g.ty = s.ty;
+        t.g.tiles_x = (nx + s.tx - 1) / s.tx;
+        t.g.tiles = t.g.tiles_x * ((ny + s.ty - 1) / s.ty);
+        return t;
+    }
+    return t;
+}
+
+int adj_waves(const AdjPlan& t) { return t.g.tiles * (t.g.threads / 64); }
+
+// The tile geometry of a launch of `steps` <= t.steps adjoint steps.
+lbk::AdjTile adj_launch(const AdjPlan& t, int steps)
+{
+    lbk::AdjTile g = t.g;
+    auto magic = [](uint32_t d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
+    g.steps = steps;
+    g.magic_tx = magic(g.tx);
+    for (int j = 0; j < steps; ++j) {
+        const int r = 3 * (steps - 1 - j) + 2;
+        g.magic_w[j] = magic(g.tx + 2 * r);
+        g.magic_2r[j] = magic(2 * r);
+        g.magic_e[j] = magic(g.tx + 2 * r + 4);
+    }
+    return g;
+}
+
+}  // namespace
+
 struct lb_adj {
     lb_ctx* fwd;          // the forward lattice (never handed out)
     lbk::AdjParams ap;
@@ -1385,15 +1472,14 @@ struct lb_adj {
     char* tapes[2];       // two regions of `every` tape entries of 4 N values
     char* tapeT;          // tape entry of the state at T
     char* lam[2];         // 9 N values each
-    char* g[2];           // N values each
-    char* gF;             // 2 N values
     char* dir;            // 2 N values
-    double* part;         // adj_blocks x 2: dL/dG from the steps
+    double* part;         // adj_waves(tile) x 2: dL/dG from the steps
     double* partE;        // adj_blocks x 2: dE/dG at T
     double* partA;        // adj_blocks: interface measure
     double* red;          // 8 reduced values
     double* drho;         // N doubles
     int blocks;
+    AdjPlan tile;         // the adjoint steps' tiles
     int32_t tape_of[2];   // segment whose tape each region holds, or -1
     bool have_forward;
     double E, A, E_target, beta, eps;
@@ -1424,16 +1510,31 @@ hipError_t adj_tape_steps(lb_adj* a, int64_t n, char* tape, hipStream_t st)
 {
     lb_ctx* c = a->fwd;
     const size_t entry = (size_t)4 * c->p.nx * c->p.ny * (a->ap.f64 ? 8 : 4);
-    for (int64_t j = 0; j < n; ++j) {
+    for (int64_t j = 0; j < n;) {
         c->coef.step = (uint32_t)c->t;
-        hipError_t e = lbk::launch_step(c->p.storage, lbk::MODE_STEP_TAPE, c->buf[c->cur],
-                                        c->buf[c->cur ^ 1], c->g, c->coef,
-                                        reinterpret_cast<double*>(tape + j * entry), st);
+        const void* src = c->buf[c->cur];
+        void* dst = c->buf[c->cur ^ 1];
+        const int k = std::max(1, tile_steps(c->tile, n - j));
+        hipError_t e;
+        if (k > 1 || (c->tile.steps && c->tile.single))
+            e = lbk::launch_tile(c->p.storage, src, dst, tile_launch(c->tile, k), c->coef, tape + j * entry, st);
+        else
+            e = lbk::launch_step(c->p.storage, lbk::MODE_STEP_TAPE, src, dst, c->g, c->coef,
+                                 reinterpret_cast<double*>(tape + j * entry), st);
         if (e) return e;
         c->cur ^= 1;
-        ++c->t;
+        c->t += k;
+        j += k;
     }
     return hipSuccess;
+}
+
+// Buffer flips of n taped forward steps (the launches of adj_tape_steps).
+int adj_tape_flips(const lb_adj* a, int64_t n)
+{
+    int flips = 0;
+    for (; n > 0; ++flips) n -= std::max(1, tile_steps(a->fwd->tile, n));
+    return flips & 1;
 }
 
 // n adjoint steps on stream st, from tape entry n - 1 down to 0, starting
@@ -1441,14 +1542,19 @@ hipError_t adj_tape_steps(lb_adj* a, int64_t n, char* tape, hipStream_t st)
 hipError_t adj_back_steps(lb_adj* a, int64_t n, const char* tape, int cur, hipStream_t st)
 {
     const size_t entry = (size_t)4 * a->ap.nx * a->ap.ny * (a->ap.f64 ? 8 : 4);
-    for (int64_t j = n - 1; j >= 0; --j) {
-        hipError_t e = lbk::adj_step(a->ap, a->lam[cur], a->g[cur], tape + j * entry,
-                                     a->lam[cur ^ 1], a->g[cur ^ 1], a->gF, a->part, st);
+    while (n > 0) {
+        const int k = even_steps(n, a->tile.steps);
+        hipError_t e = lbk::adj_steps(a->ap, adj_launch(a->tile, k), a->lam[cur], tape + (n - 1) * entry,
+                                      a->lam[cur ^ 1], a->part, st);
         if (e) return e;
         cur ^= 1;
+        n -= k;
     }
     return hipSuccess;
 }
+
+// Adjoint buffer flips of n steps.
+int adj_flips(const lb_adj* a, int64_t n) { return (int)((n + a->tile.steps - 1) / a->tile.steps & 1); }
 
 void adj_drop_graphs(lb_adj* a)
 {
@@ -1510,7 +1616,7 @@ hipError_t adj_restep(lb_adj* a, int32_t s)
         auto work = [&] { return adj_tape_steps(a, n, a->tapes[b], st); };
         if (n == a->every) {
             e = adj_replay(a, a->tape_graphs, b, st, work);
-            c->cur = (int)(n & 1);
+            c->cur = adj_tape_flips(a, n);
             c->t = t0 + n;
         } else {
             e = work();
@@ -1546,10 +1652,11 @@ int check_adj(lb_adj* a)
 
 struct AdjLayout {
     lb_params fp;         // forward parameters: no trace
-    size_t fwd, fwd_bytes, ckpt, ckpt_bytes, tape[2], tapeT, lam[2], g[2], gF, dir, part, partE, partA,
+    size_t fwd, fwd_bytes, ckpt, ckpt_bytes, tape[2], tapeT, lam[2], dir, part, partE, partA,
         red, drho, total;
     int32_t nseg;
     int blocks;
+    AdjPlan tile;
 };
 
 int adj_layout(const lb_params* p, int64_t nsteps, int32_t every, AdjLayout* L)
@@ -1588,10 +1695,9 @@ int adj_layout(const lb_params* p, int64_t nsteps, int32_t every, AdjLayout* L)
     if (nseg > 1) { L->tape[1] = off; off += align_up((size_t)seg_len * 4 * N * es); }
     L->tapeT = off; off += align_up((size_t)4 * N * es);
     for (int q = 0; q < 2; ++q) { L->lam[q] = off; off += align_up((size_t)9 * N * es); }
-    for (int q = 0; q < 2; ++q) { L->g[q] = off; off += align_up((size_t)N * es); }
-    L->gF = off; off += align_up((size_t)2 * N * es);
     L->dir = off; off += align_up((size_t)2 * N * es);
-    L->part = off; off += align_up((size_t)L->blocks * 2 * sizeof(double));
+    L->tile = adj_plan(p->nx, p->ny, p->storage == LB_F64);
+    L->part = off; off += align_up((size_t)adj_waves(L->tile) * 2 * sizeof(double));
     L->partE = off; off += align_up((size_t)L->blocks * 2 * sizeof(double));
     L->partA = off; off += align_up((size_t)L->blocks * sizeof(double));
     L->red = off; off += align_up(8 * sizeof(double));
@@ -1645,11 +1751,7 @@ int lb_adj_init(lb_adj** out, const lb_params* p, int64_t nsteps, int32_t checkp
         a->tape_of[q] = -1;
     }
     a->tapeT = ws + L.tapeT;
-    for (int q = 0; q < 2; ++q) {
-        a->lam[q] = ws + L.lam[q];
-        a->g[q] = ws + L.g[q];
-    }
-    a->gF = ws + L.gF;
+    for (int q = 0; q < 2; ++q) a->lam[q] = ws + L.lam[q];
     a->dir = ws + L.dir;
     a->part = reinterpret_cast<double*>(ws + L.part);
     a->partE = reinterpret_cast<double*>(ws + L.partE);
@@ -1657,6 +1759,7 @@ int lb_adj_init(lb_adj** out, const lb_params* p, int64_t nsteps, int32_t checkp
     a->red = reinterpret_cast<double*>(ws + L.red);
     a->drho = reinterpret_cast<double*>(ws + L.drho);
     a->blocks = L.blocks;
+    a->tile = L.tile;
     a->have_forward = false;
     a->graph_G1 = a->ap.G1;
     a->graph_G2 = a->ap.G2;
@@ -1791,8 +1894,8 @@ int lb_adj_backward(lb_adj* a, double dG[2], double* drho, int on_device)
     const double two_dE = 2.0 * (a->E - a->E_target);
     hipError_t e;
     if ((e = lbk::adj_area(a->ap, a->tapeT, a->eps, a->dir, a->partA, st)) ||
-        (e = lbk::adj_seed(a->ap, a->tapeT, a->dir, two_dE, a->beta, a->lam[0], a->g[0], a->partE, st)) ||
-        (e = lbk::adj_zero(a->part, (int64_t)a->blocks * 2, st)))
+        (e = lbk::adj_seed(a->ap, a->tapeT, a->dir, two_dE, a->beta, a->lam[0], a->partE, st)) ||
+        (e = lbk::adj_zero(a->part, (int64_t)adj_waves(a->tile) * 2, st)))
         return hip_fail(e, "adjoint seed");
     if (a->use_graphs && (a->graph_G1 != a->ap.G1 || a->graph_G2 != a->ap.G2)) {
         adj_drop_graphs(a);
@@ -1812,11 +1915,11 @@ int lb_adj_backward(lb_adj* a, double dG[2], double* drho, int on_device)
         if ((e = adj_backseg(a, s, cur))) return hip_fail(e, "adjoint steps");
         const int64_t t0 = (int64_t)s * a->every;
         const int64_t n = a->T - t0 < a->every ? a->T - t0 : a->every;
-        cur ^= (int)(n & 1);
+        cur ^= adj_flips(a, n);
     }
     double* dst = on_device ? drho : a->drho;
-    if ((e = lbk::adj_rho_grad(a->ap, a->lam[cur], a->g[cur], dst, st)) ||
-        (e = lbk::adj_reduce(a->part, a->blocks, 2, a->red + 2, st)) ||
+    if ((e = lbk::adj_rho_grad(a->ap, a->lam[cur], dst, st)) ||
+        (e = lbk::adj_reduce(a->part, adj_waves(a->tile), 2, a->red + 2, st)) ||
         (e = lbk::adj_reduce(a->partE, a->blocks, 2, a->red + 4, st)))
         return hip_fail(e, "adjoint reductions");
     double r[4];

@@ -165,19 +165,33 @@ int adj_blocks(int64_t sites);
 // population buffer of the given storage (ST_F64 or ST_F32).
 hipError_t adj_tape(int storage, const void* buf, const Geom& g, const AdjParams& p, void* tape,
                     hipStream_t s);
-// One adjoint step: (lam_next, g_next) at t+1 -> (lam, g) at t; gF[2][ny][nx]
-// is scratch; part[adj_blocks][2] accumulates dL/dG1, dL/dG2.
-hipError_t adj_step(const AdjParams& p, const void* lam_next, const void* g_next, const void* tape,
-                    void* lam, void* g, void* gF, double* part, hipStream_t s);
+// Adjoint steps in one launch: tiles of tx x ty sites, at most kAdjTileMax
+// squared, whose halo of 3 steps - 1 sites holds at most as many again.  The
+// tile with 3 steps + 1 sites more on each side wraps around the lattice at
+// most once.
+constexpr int kAdjTileMax = 32, kAdjMaxSteps = 5;
+struct AdjTile {
+    int32_t tx, ty, tiles_x, tiles, threads;
+    int32_t steps;  // of this launch
+    uint32_t magic_tx;                                         // division by tx, and by step:
+    uint32_t magic_w[kAdjMaxSteps], magic_2r[kAdjMaxSteps];    // by the halo region's width, twice the halo
+    uint32_t magic_e[kAdjMaxSteps];                            // by that width + 4
+};
+// `steps` adjoint steps: lam_in[9][ny][nx] at t -> lam_out at t - steps, from
+// the tape entry of t - 1 at `tape` and the earlier ones before it;
+// part[tiles * threads / 64][2] accumulates dL/dG1, dL/dG2, the same bits for
+// any split of a run into launches.
+hipError_t adj_steps(const AdjParams& p, const AdjTile& g, const void* lam_in, const void* tape, void* lam_out,
+                     double* part, hipStream_t s);
 // Interface measure of a tape entry: dir[2][ny][nx], part[adj_blocks] sums.
 hipError_t adj_area(const AdjParams& p, const void* tape, double eps, void* dir, double* part,
                     hipStream_t s);
 // Adjoint at T of L = (E - E*)^2 + beta A; part[adj_blocks][2] receives the
 // workgroup sums of dE/dG1, dE/dG2.
 hipError_t adj_seed(const AdjParams& p, const void* tape, const void* dir, double two_dE, double beta,
-                    void* lam, void* g, double* part, hipStream_t s);
-// out[ny][nx] (double) = sum_i w_i (lam_i + g).
-hipError_t adj_rho_grad(const AdjParams& p, const void* lam, const void* g, double* out, hipStream_t s);
+                    void* lam, double* part, hipStream_t s);
+// out[ny][nx] (double) = sum_i w_i lam_i.
+hipError_t adj_rho_grad(const AdjParams& p, const void* lam, double* out, hipStream_t s);
 // out[v] = sum_b part[b * nv + v] for v < nv, fixed order.
 hipError_t adj_reduce(const double* part, int blocks, int nv, double* out, hipStream_t s);
 hipError_t adj_zero(double* p, int64_t n, hipStream_t s);
