@@ -323,8 +323,8 @@ int lb_adj_destroy(lb_adj* a);
  *         n = 0 .. nshell-1 (every mode lies in exactly one shell);
  *   kbar = sum_n n S_n / sum_n S_n (eq. rad, k in units of 2 pi / L);
  *   the droplet length scale is then R = L / (2 kbar) (k = 1 gives L/2).
- * Computed in double precision by FFTs in LDS (a direct transform when L is
- * not a power of two); every sum has a fixed order, so repeated calls give
+ * Computed in double precision by FFTs in LDS (radices 2 to 8, by
+ * convolution when L has a prime factor above 7); every sum has a fixed order, so repeated calls give
  * bit-identical results.  Workspace and stream rules are those of lb_init.
  * ------------------------------------------------------------------------ */
 typedef struct lb_sk lb_sk;

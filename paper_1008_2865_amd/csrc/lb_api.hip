@@ -1993,7 +1993,8 @@ int sk_check_L(int32_t L)
 }
 
 struct SkLayout {
-    size_t tw, z, spec, part, count, rho, total;
+    lbk::SkFft fft;
+    size_t tw, chirp, filter, z, spec, part, count, rho, total;
     int32_t nshell, hc, hp;
 };
 
@@ -2005,8 +2006,11 @@ SkLayout sk_layout(int32_t L)
     S.nshell = (int32_t)shell_of(2 * h * h) + 1;
     S.hc = (L + 1) / 2;
     S.hp = (int32_t)h + 1;
+    S.fft = lbk::sk_fft(L);
     size_t off = 0;
-    S.tw = off; off += align_up((size_t)L * 2 * sizeof(double));
+    S.tw = off; off += align_up((size_t)S.fft.m * 2 * sizeof(double));
+    S.chirp = off; off += align_up((size_t)L * 2 * sizeof(double));
+    S.filter = off; off += align_up((size_t)S.fft.m * 2 * sizeof(double));
     S.z = off; off += align_up((size_t)L * S.hc * 2 * sizeof(double));
     S.spec = off; off += align_up((size_t)S.hp * L * sizeof(double));
     S.part = off; off += align_up((size_t)S.nshell * S.hp * sizeof(double));
@@ -2068,7 +2072,7 @@ int lb_sk_init(lb_sk** out, int32_t L, void* workspace, size_t bytes, void* hip_
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     lb_sk* s = new lb_sk();
     lbk::SkPlan& p = s->plan;
-    p.fft = lbk::sk_fft(L);
+    p.fft = S.fft;
     p.nshell = S.nshell;
     p.hc = S.hc;
     p.hp = S.hp;
@@ -2079,9 +2083,13 @@ int lb_sk_init(lb_sk** out, int32_t L, void* workspace, size_t bytes, void* hip_
     p.log_cols = 2;
     while (p.log_cols > 0 &&
            ((p.hc + (1 << p.log_cols) - 1) >> p.log_cols < 256 ||
-            lbk::sk_column_lds(L, 1 << p.log_cols, p.fft.any != 0) > (size_t)lbk::kSkColumnLds))
+            p.fft.m << p.log_cols > 8192 ||
+            lbk::sk_lds(p.fft, 1 << p.log_cols) > (size_t)lbk::kSkColumnLds))
         --p.log_cols;
-    p.tw = reinterpret_cast<double2*>(ws + S.tw);
+    double2* tw = reinterpret_cast<double2*>(ws + S.tw);
+    double2* chirp = reinterpret_cast<double2*>(ws + S.chirp);
+    double2* filter = reinterpret_cast<double2*>(ws + S.filter);
+    p.t = lbk::SkTables{tw, chirp, filter};
     p.z = reinterpret_cast<double2*>(ws + S.z);
     p.spec = reinterpret_cast<double*>(ws + S.spec);
     p.part = reinterpret_cast<double*>(ws + S.part);
@@ -2102,7 +2110,7 @@ int lb_sk_init(lb_sk** out, int32_t L, void* workspace, size_t bytes, void* hip_
     if ((e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p.shell), s->host_shell, 0)) ||
         (e = hipMemcpyAsync(ws + S.count, counts.data(), counts.size() * sizeof(double),
                             hipMemcpyHostToDevice, st)) ||
-        (e = lbk::sk_prepare(p, st)) || (e = hipStreamSynchronize(st))) {
+        (e = lbk::sk_prepare(p, tw, chirp, filter, st)) || (e = hipStreamSynchronize(st))) {
         (void)hipHostFree(s->host_shell);
         delete s;
         return hip_fail(e, "structure-factor tables");

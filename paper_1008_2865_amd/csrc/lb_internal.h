@@ -200,14 +200,22 @@ hipError_t adj_zero(double* p, int64_t n, hipStream_t s);
 constexpr int kSkMaxL = 2048;
 // LDS a workgroup of the column pass may use (160 KB less its static part).
 constexpr int kSkColumnLds = 159 * 1024;
-// Passes of a mixed-radix transform of n points: radix[p] after sub-transforms
-// of length s (the product of the radices before it), with the multipliers
-// that divide by s and by n / radix[p].
+// The transform of n points: its passes over m points, m = n or, where n has a
+// prime factor above 7, a smooth m >= 2 n - 1 (by convolution: two transforms
+// of m points); radix[p] after sub-transforms of length s (the product of the
+// radices before it), with the multipliers that divide by s and by
+// m / radix[p].  The line lies at 7: as radices, 11 and 13 took 98 us for
+// 1001^2, the convolution 67 for 1003^2.
 struct SkFft {
-    int32_t n, passes;
-    int32_t any;  // some radix is a prime above 5
+    int32_t n, m, passes;
+    int32_t chirp;  // by convolution
     int32_t radix[12];
     uint32_t magic_s[12], magic_m[12];
+};
+struct SkTables {
+    const double2* tw;      // m twiddles exp(-2 pi i k / m)
+    const double2* chirp;   // n (with SkFft::chirp)
+    const double2* filter;  // m
 };
 struct SkPlan {
     SkFft fft;
@@ -215,7 +223,7 @@ struct SkPlan {
     int32_t hc;          // columns of the row spectra: L/2, (L+1)/2 for odd L
     int32_t log_cols;    // columns per workgroup of the column pass, log2
     int32_t hp;          // L/2 + 1, columns of the half spectrum
-    double2* tw;         // L twiddles exp(-2 pi i k / L)
+    SkTables t;
     double2* z;          // L*hc: row spectra, [y][l]
     double* spec;        // hp*L: S at (l, m), l <= L/2, stored [l][m]
     double* part;        // nshell*hp: run sums, [n][l]
@@ -223,12 +231,12 @@ struct SkPlan {
     double* shell;       // nshell shell averages (pinned host memory)
 };
 SkFft sk_fft(int L);
-// LDS of the column pass with `cols` columns per workgroup.
-size_t sk_column_lds(int L, int cols, bool any);
+// LDS of a workgroup with `cols` lines.
+size_t sk_lds(const SkFft& f, int cols);
 // Runs every pass on rho (device, L*L doubles); spectrum (device, [m][l])
 // may be NULL.
 hipError_t sk_compute(const SkPlan& p, const double* rho, double* spectrum, hipStream_t s);
-// Fills p.tw (once per plan).
-hipError_t sk_prepare(const SkPlan& p, hipStream_t s);
+// Fills the tables of p.t (once per plan).
+hipError_t sk_prepare(const SkPlan& p, double2* tw, double2* chirp, double2* filter, hipStream_t s);
 
 }  // namespace lbk

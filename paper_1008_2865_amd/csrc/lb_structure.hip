@@ -22,11 +22,14 @@
 // rate.  The passes move 33.5 MB of density, 33.6 MB of row spectra out and
 // in again, and 2 x 6 MB of run sums, where a full complex transform with a
 // transpose and a gather of every mode into its shell moved 386 MB.  A whole
-// evaluation on MI355X: 2048^2 241 -> 70 us, 1000^2 with the full spectrum
-// 1416 -> 59 us (radices 8, 5, 5, 5 in place of the direct sum), 512^2 41 us.
+// evaluation on MI355X: 2048^2 238 -> 70 us, 1000^2 (radices 8, 5, 5, 5 in
+// place of the direct sum) 1418 -> 51, 521^2 (by convolution) 346 -> 60, 2039^2
+// 9424 -> 152, 512^2 41, 40^2 74 -> 31.
 #include "lb_internal.h"
 
 #include <hip/hip_runtime.h>
+
+#include <initializer_list>
 
 namespace lbk {
 namespace {
@@ -114,6 +117,36 @@ __device__ __forceinline__ void dft(double2 (&v)[5])
     v[2] = add(a2, b2);
     v[3] = sub(a2, b2);
 }
+__device__ __forceinline__ void dft(double2 (&v)[7])
+{
+    // cos and sin of 2 pi k / 7, k = 1 .. 3.
+    constexpr double kC[3] = {0.62348980185873353053, -0.22252093395631440429, -0.90096886790241912624};
+    constexpr double kS[3] = {0.78183148246802980871, 0.97492791218182360702, 0.43388373911755812048};
+    double2 t[3], d[3], out[7];
+    out[0] = v[0];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        t[q] = add(v[q + 1], v[6 - q]);
+        d[q] = sub(v[q + 1], v[6 - q]);
+        out[0] = add(out[0], t[q]);
+    }
+#pragma unroll
+    for (int p = 1; p < 4; ++p) {
+        double2 a = v[0], b = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int k = p * (q + 1) % 7, m = k > 3 ? 7 - k : k;  // cos k = cos m, sin k = -sin m beyond 3
+            const double sn = k > 3 ? -kS[m - 1] : kS[m - 1];
+            a = make_double2(a.x + kC[m - 1] * t[q].x, a.y + kC[m - 1] * t[q].y);
+            b = make_double2(b.x + sn * d[q].x, b.y + sn * d[q].y);
+        }
+        b = mul_mi(b);
+        out[p] = add(a, b);
+        out[7 - p] = sub(a, b);
+    }
+#pragma unroll
+    for (int p = 0; p < 7; ++p) v[p] = out[p];
+}
 __device__ __forceinline__ void dft(double2 (&v)[8])
 {
     constexpr double kH = 0.70710678118654752440;
@@ -184,73 +217,86 @@ fft_pass(double2* x, int lines, int lp, int n, int s, uint32_t magic_s, uint32_t
     __syncthreads();
 }
 
-// A pass of any other radix r (a prime factor of L): output o of a line is
-// the sum of r products, x[j + q L/r] w_L^{q e mod L} with e = (o mod r s)
-// L / (r s), each thread forming its outputs one by one; twl is the twiddle
-// table in LDS.  For a prime L this is the direct transform.
+// All passes of `lines` lines of length f.m, line c at x[c lp + pad(i)].
+// Needs lines * f.m <= kPerThread * blockDim.x, and a barrier before it.
 __device__ __forceinline__ void
-any_pass(double2* x, int lines, int lp, int n, int r, int s, const double2* twl)
-{
-    const int T = blockDim.x, tid = threadIdx.x;
-    const int m = n / r, rs = r * s, estep = n / rs, total = lines * n;
-    double2 acc[kPerThread];
-    int line[kPerThread], j[kPerThread], e[kPerThread], t[kPerThread];
-#pragma unroll
-    for (int b = 0; b < kPerThread; ++b) {
-        const int idx = min(tid + b * T, total - 1);
-        const int c = idx / n, o = idx - c * n;
-        const int blk = o / rs, rem = o - blk * rs;
-        line[b] = c * lp;
-        j[b] = blk * s + rem % s;
-        e[b] = rem * estep;
-        t[b] = 0;
-        acc[b] = make_double2(0.0, 0.0);
-    }
-    for (int q = 0; q < r; ++q) {
-#pragma unroll
-        for (int b = 0; b < kPerThread; ++b) {
-            if (tid + b * T >= total) continue;
-            const double2 v = x[line[b] + pad(j[b] + q * m)];
-            const double2 w = twl[t[b]];
-            acc[b].x += v.x * w.x - v.y * w.y;
-            acc[b].y += v.x * w.y + v.y * w.x;
-            t[b] += e[b];
-            t[b] = t[b] >= n ? t[b] - n : t[b];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < kPerThread; ++b) {
-        const int idx = tid + b * T;
-        if (idx >= total) continue;
-        const int c = idx / n;
-        x[c * lp + pad(idx - c * n)] = acc[b];
-    }
-    __syncthreads();
-}
-
-// All passes of `lines` lines of length f.n, line c at x[c lp + pad(i)].
-// Needs lines * f.n <= kPerThread * blockDim.x, and a barrier before it.
-template <bool kAny>
-__device__ __forceinline__ void
-fft_lines(double2* x, int lines, int lp, const SkFft& f, const double2* __restrict__ tw,
-          const double2* twl)
+fft_passes(double2* x, int lines, int lp, const SkFft& f, const double2* __restrict__ tw)
 {
     int s = 1;
     for (int p = 0; p < f.passes; ++p) {
         const int r = f.radix[p];
         const uint32_t ms = f.magic_s[p], mm = f.magic_m[p];
         switch (r) {
-        case 8: fft_pass<8>(x, lines, lp, f.n, s, ms, mm, tw); break;
-        case 4: fft_pass<4>(x, lines, lp, f.n, s, ms, mm, tw); break;
-        case 2: fft_pass<2>(x, lines, lp, f.n, s, ms, mm, tw); break;
-        case 3: fft_pass<3>(x, lines, lp, f.n, s, ms, mm, tw); break;
-        case 5: fft_pass<5>(x, lines, lp, f.n, s, ms, mm, tw); break;
-        default:
-            if constexpr (kAny) any_pass(x, lines, lp, f.n, r, s, twl);
-            break;
+        case 8: fft_pass<8>(x, lines, lp, f.m, s, ms, mm, tw); break;
+        case 4: fft_pass<4>(x, lines, lp, f.m, s, ms, mm, tw); break;
+        case 2: fft_pass<2>(x, lines, lp, f.m, s, ms, mm, tw); break;
+        case 3: fft_pass<3>(x, lines, lp, f.m, s, ms, mm, tw); break;
+        case 5: fft_pass<5>(x, lines, lp, f.m, s, ms, mm, tw); break;
+        default: fft_pass<7>(x, lines, lp, f.m, s, ms, mm, tw); break;
         }
         s *= r;
+    }
+}
+
+// The transform of `lines` lines of length f.n.  A length with a prime factor
+// above 7 goes by Bluestein's convolution: with b_i = e^{i pi i^2 / n},
+//   X_k = b*_k sum_i (x_i b*_i) b_{k-i},
+// a cyclic convolution of a smooth length f.m >= 2 n - 1: transform x b*, times
+// the transform of b (over m), inverse transform (by conjugation).  The line
+// then holds f.m elements.
+template <bool kChirp>
+__device__ __forceinline__ void
+fft_lines(double2* x, int lines, int lp, const SkFft& f, const SkTables& t)
+{
+    if constexpr (!kChirp) {
+        fft_passes(x, lines, lp, f, t.tw);
+    } else {
+        const int T = blockDim.x, tid = threadIdx.x, m = f.m;
+        // This thread's elements of the lines, each time the same.
+        auto each = [&](auto&& fn) {
+#pragma unroll
+            for (int b = 0; b < kPerThread; ++b) {
+                const int idx = tid + b * T;
+                if (idx >= lines * m) break;
+                const int c = idx / m, i = idx - c * m;
+                fn(x[c * lp + pad(i)], i);
+            }
+            __syncthreads();
+        };
+        auto conj = [](double2 v) { return make_double2(v.x, -v.y); };
+        each([&](double2& v, int i) { v = i < f.n ? mul(v, conj(t.chirp[i])) : make_double2(0.0, 0.0); });
+        fft_passes(x, lines, lp, f, t.tw);
+        each([&](double2& v, int i) { v = conj(mul(v, t.filter[i])); });
+        fft_passes(x, lines, lp, f, t.tw);
+        each([&](double2& v, int i) {
+            if (i < f.n) v = conj(mul(v, t.chirp[i]));
+        });
+    }
+}
+
+// chirp[i] = e^{i pi i^2 / n}, i < n, and the filter: its transform as a
+// cyclic sequence of length m (b_i at i and m - i), over m.  One workgroup.
+__global__ void __launch_bounds__(512)
+k_sk_chirp(SkFft f, const double2* __restrict__ tw, double2* __restrict__ chirp, double2* __restrict__ filter)
+{
+    extern __shared__ double2 lds[];
+    const int n = f.n, m = f.m;
+    for (int i = threadIdx.x; i < m; i += blockDim.x) {
+        const int d = min(i, m - i);  // distance on the cycle
+        double2 v = make_double2(0.0, 0.0);
+        if (d < n) {
+            double sn, cs;
+            sincospi((double)((int64_t)d * d % (2 * n)) / (double)n, &sn, &cs);
+            v = make_double2(cs, sn);
+            if (i < n) chirp[i] = v;
+        }
+        lds[pad(i)] = v;
+    }
+    __syncthreads();
+    fft_passes(lds, 1, 0, f, tw);
+    for (int i = threadIdx.x; i < m; i += blockDim.x) {
+        const double2 v = lds[pad(i)];
+        filter[i] = make_double2(v.x / (double)m, v.y / (double)m);
     }
 }
 
@@ -291,18 +337,15 @@ __device__ __forceinline__ double pairwise(const double (&v)[kPerThread])
 // less its own mean (which only l = 0 carries: that entry is the row's sum,
 // formed before the subtraction).  z[y][l], l < hc: the row spectra for
 // l = 0 .. hc - 1; for even L the real values at l = 0 and l = L/2 share
-// entry 0, as its real and imaginary part.  LDS: pad(L) + 2 elements, with
-// kAny L twiddles more.
-template <bool kAny>
-__global__ void __launch_bounds__(kThreads)
-k_sk_rows(const double* __restrict__ rho, SkFft f, const double2* __restrict__ tw, int hc,
-          double2* __restrict__ z)
+// entry 0, as its real and imaginary part.  LDS: pad(f.m) + 2 elements.
+template <bool kChirp>
+__global__ void __launch_bounds__(kChirp ? 512 : 256)
+k_sk_rows(const double* __restrict__ rho, SkFft f, SkTables t, int hc, double2* __restrict__ z)
 {
     extern __shared__ double2 lds[];
     __shared__ double red[2 * 16];
     const int n = f.n, tid = threadIdx.x, T = blockDim.x;
     double2* x = lds;
-    double2* twl = lds + pad(n) + 2;
     const int64_t ya = 2 * (int64_t)blockIdx.x;
     const bool two = ya + 1 < n;
     const double* ra = rho + ya * n;
@@ -314,8 +357,6 @@ k_sk_rows(const double* __restrict__ rho, SkFft f, const double2* __restrict__ t
         va[b] = i < n ? ra[i] : 0.0;
         vb[b] = i < n ? rb[i] : 0.0;
     }
-    if (kAny)
-        for (int i = tid; i < n; i += T) twl[i] = tw[i];
     double sum[2] = {pairwise(va), pairwise(vb)};
     block_sum<2>(sum, red);
     const double ma = sum[0] / (double)n, mb = sum[1] / (double)n;
@@ -325,7 +366,7 @@ k_sk_rows(const double* __restrict__ rho, SkFft f, const double2* __restrict__ t
         if (i < n) x[pad(i)] = make_double2(va[b] - ma, vb[b] - mb);
     }
     __syncthreads();
-    fft_lines<kAny>(x, 1, 0, f, tw, twl);
+    fft_lines<kChirp>(x, 1, 0, f, t);
     double2* za = z + ya * hc;
     double2* zb = za + hc;
     for (int k = tid; k < hc; k += T) {
@@ -368,20 +409,19 @@ __device__ __forceinline__ int shell_at(int l, int h)
 // `cols` columns per workgroup (a power of two, log2 = lc).  spec (may be
 // NULL): S at [l][m], l = 0 .. L/2.  part[n][l], pitch hp: the sum of S over
 // the modes (+-l, m) of shell n, each m in ascending order with its -m.  LDS:
-// cols (pad(L) + 2) elements, with kAny L twiddles more.  A segment of four
-// columns is 64 bytes of a row of z.
-template <bool kAny>
+// cols (pad(f.m) + 2) elements.  A segment of four columns is 64 bytes of a row
+// of z.
+template <bool kChirp>
 __global__ void __launch_bounds__(1024)
-k_sk_columns(const double2* __restrict__ z, SkFft f, const double2* __restrict__ tw, int hc, int lc,
-             double invN, double* __restrict__ spec, double* __restrict__ part, int hp)
+k_sk_columns(const double2* __restrict__ z, SkFft f, SkTables t, int hc, int lc, double invN,
+             double* __restrict__ spec, double* __restrict__ part, int hp)
 {
     extern __shared__ double2 lds[];
     __shared__ double red[16];
     const int n = f.n, tid = threadIdx.x, T = blockDim.x;
-    const int cols = 1 << lc, lp = pad(n) + 2, h = n / 2;
+    const int cols = 1 << lc, lp = pad(f.m) + 2, h = n / 2;
     const bool even = (n & 1) == 0;
     double2* x = lds;
-    double2* twl = lds + cols * lp;
     // Consecutive column groups share the lines of z: keep them on one XCD.
     const int per_xcd = gridDim.x / 8, rem = gridDim.x % 8, xcd = blockIdx.x % 8;
     const int group = xcd * per_xcd + min(xcd, rem) + blockIdx.x / 8;
@@ -399,8 +439,6 @@ k_sk_columns(const double2* __restrict__ z, SkFft f, const double2* __restrict__
             const int i = tid + b * T, y = i >> lc, c = i & (cols - 1);
             if (y < n) x[c * lp + pad(y)] = v[b];
         }
-        if (kAny)
-            for (int i = tid; i < n; i += T) twl[i] = tw[i];
         if (l0 == 0) {
             // Column l = 0 (real parts): the rows' sums, less their mean.
             double s[kPerThread];
@@ -420,7 +458,7 @@ k_sk_columns(const double2* __restrict__ z, SkFft f, const double2* __restrict__
         }
     }
     __syncthreads();
-    fft_lines<kAny>(x, cols, lp, f, tw, twl);
+    fft_lines<kChirp>(x, cols, lp, f, t);
 
     // S in place: .x of every column; for column 0 the columns l = 0 (.x)
     // and, for even L, l = L/2 (.y), separated as in k_sk_rows.
@@ -507,65 +545,74 @@ k_sk_spread(const double* __restrict__ in, int L, double* __restrict__ out)
     }
 }
 
-template <bool kAny>
+// Whole waves of kPerThread values a thread.
+dim3 lanes(int values) { return dim3((values + 64 * kPerThread - 1) / (64 * kPerThread) * 64); }
+
+template <bool kChirp>
 hipError_t passes(const SkPlan& p, const double* rho, double* spec, hipStream_t s)
 {
-    const int n = p.fft.n;
-    // Whole waves of kPerThread values a thread.
-    auto lanes = [](int values) { return dim3((values + 64 * kPerThread - 1) / (64 * kPerThread) * 64); };
-    hipLaunchKernelGGL(k_sk_rows<kAny>, dim3((n + 1) / 2), lanes(n), sk_column_lds(n, 1, kAny), s, rho, p.fft, p.tw, p.hc,
-                       p.z);
-    const int cols = 1 << p.log_cols;
-    hipLaunchKernelGGL(k_sk_columns<kAny>, dim3((p.hc + cols - 1) / cols), lanes(n * cols),
-                       sk_column_lds(n, cols, kAny), s, p.z, p.fft, p.tw, p.hc, p.log_cols,
-                       1.0 / ((double)n * (double)n), spec, p.part, p.hp);
+    const SkFft& f = p.fft;
+    const int n = f.n, cols = 1 << p.log_cols;
+    hipLaunchKernelGGL(k_sk_rows<kChirp>, dim3((n + 1) / 2), lanes(f.m), sk_lds(f, 1), s, rho, f, p.t, p.hc, p.z);
+    hipLaunchKernelGGL(k_sk_columns<kChirp>, dim3((p.hc + cols - 1) / cols), lanes(f.m * cols), sk_lds(f, cols), s,
+                       p.z, f, p.t, p.hc, p.log_cols, 1.0 / ((double)n * (double)n), spec, p.part, p.hp);
     return hipGetLastError();
 }
 
 }  // namespace
 
-size_t sk_column_lds(int L, int cols, bool any)
+size_t sk_lds(const SkFft& f, int cols)
 {
-    return ((size_t)(pad(L) + 2) * cols + (any ? L : 0)) * sizeof(double2);
+    return (size_t)(pad(f.m) + 2) * cols * sizeof(double2);
 }
 
 SkFft sk_fft(int L)
 {
     SkFft f{};
-    f.n = L;
+    f.n = f.m = L;
+    auto smooth = [](int v, std::initializer_list<int> primes) {
+        for (int r : primes)
+            while (v % r == 0) v /= r;
+        return v == 1;
+    };
+    if (!smooth(L, {2, 3, 5, 7})) {
+        // The smallest length of factors 2, 3, 5 that is a multiple of 8.
+        f.chirp = 1;
+        for (f.m = (2 * L - 1 + 7) / 8 * 8; !smooth(f.m, {2, 3, 5});) f.m += 8;
+    }
     auto magic = [](int d) { return d > 1 ? (uint32_t)(((uint64_t(1) << 32) + d - 1) / d) : 0u; };
-    // Radices 8, 4, 2, 5, 3, then the primes from 7 up.
-    const int first[5] = {8, 4, 2, 5, 3};
-    for (int s = 1, k = 0; s < L; ++k) {
-        const int r = k < 5 ? first[k] : 7 + 2 * (k - 5);
-        for (; L / s % r == 0; s *= r) {
+    int s = 1;
+    for (int r : {8, 4, 2, 5, 3, 7})
+        for (; f.m / s % r == 0; s *= r) {
             f.radix[f.passes] = r;
             f.magic_s[f.passes] = magic(s);
-            f.magic_m[f.passes] = magic(L / r);
+            f.magic_m[f.passes] = magic(f.m / r);
             ++f.passes;
-            if (k >= 5) f.any = 1;
         }
-    }
     return f;
 }
 
-hipError_t sk_prepare(const SkPlan& p, hipStream_t s)
+hipError_t sk_prepare(const SkPlan& p, double2* tw, double2* chirp, double2* filter, hipStream_t s)
 {
-    // The column pass of a 2048-point line keeps four of them in LDS: 144 KB.
-    for (const void* fn : {reinterpret_cast<const void*>(k_sk_columns<true>),
-                           reinterpret_cast<const void*>(k_sk_columns<false>)}) {
+    // Four columns of 2048 points take 144 KB of LDS.
+    for (const void* fn : {reinterpret_cast<const void*>(k_sk_columns<false>),
+                           reinterpret_cast<const void*>(k_sk_columns<true>),
+                           reinterpret_cast<const void*>(k_sk_rows<true>),
+                           reinterpret_cast<const void*>(k_sk_chirp)}) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kSkColumnLds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_sk_twiddles, dim3((p.fft.n + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
-                       p.fft.n, p.tw);
+    const SkFft& f = p.fft;
+    hipLaunchKernelGGL(k_sk_twiddles, dim3((f.m + kThreads - 1) / kThreads), dim3(kThreads), 0, s, f.m, tw);
+    if (f.chirp)
+        hipLaunchKernelGGL(k_sk_chirp, dim3(1), lanes(f.m), sk_lds(f, 1), s, f, tw, chirp, filter);
     return hipGetLastError();
 }
 
 hipError_t sk_compute(const SkPlan& p, const double* rho, double* spectrum, hipStream_t s)
 {
     double* spec = spectrum ? p.spec : nullptr;
-    const hipError_t e = p.fft.any ? passes<true>(p, rho, spec, s) : passes<false>(p, rho, spec, s);
+    const hipError_t e = p.fft.chirp ? passes<true>(p, rho, spec, s) : passes<false>(p, rho, spec, s);
     if (e) return e;
     const int L = p.fft.n, per = kThreads / 64;
     hipLaunchKernelGGL(k_sk_shells, dim3((p.nshell + per - 1) / per), dim3(kThreads), 0, s, p.part, p.hp, L,

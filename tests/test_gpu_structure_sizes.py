@@ -1,10 +1,10 @@
 """GPU: the structure factor over the factorisations its transform meets.
 
-Sides with every radix of the mixed-radix passes (8, 4, 2, 5, 3, primes),
-odd sides (no l = L/2 column), sides whose columns run one, two and four to a
-workgroup, and the smallest and largest of the range, against the oracle.
-Tolerances are those of the random-field test: the transforms' rounding is a
-few ulp per pass, or of order sqrt(p) ulp for a prime factor p, far below.
+Sides with every radix of the mixed-radix passes (8, 4, 2, 5, 3, 7), sides by
+convolution (a prime factor above 7), odd sides (no l = L/2 column), sides whose
+columns run one, two and four to a workgroup, and the smallest and largest of
+the range, against the oracle.  Tolerances are those of the random-field test:
+the transforms' rounding is a few ulp per pass, far below.
 """
 import numpy as np
 import pytest
@@ -21,7 +21,7 @@ if not torch.cuda.is_available():
 from paper_1008_2865_amd.structure import StructureFactor  # noqa: E402
 
 
-@pytest.mark.parametrize("L", [5, 6, 7, 9, 16, 33, 128, 250, 331, 540, 662, 1000, 1021, 1025, 1536, 2002, 2045,
+@pytest.mark.parametrize("L", [5, 6, 7, 9, 11, 16, 33, 49, 128, 250, 331, 540, 662, 700, 1000, 1021, 1025, 1372, 1536, 2002, 2045,
                                2046, 2047])
 def test_sides_match_oracle(L):
     print(f"structure factor L={L}", flush=True)
