@@ -155,8 +155,9 @@ int lb_moments(lb_ctx* c, double* rho, double* ux, double* uy, int on_device);
  * (rest weight p_s0 = 247/420 from eq. weights_1) and
  * E_m = 1/2 sum_x psi(x) sum_{i=1}^{16} G2 p_mi psi(x + c_mi).
  * Sums are in double, in an order fixed by the launch shape, so repeated
- * runs give bit-identical values.  LB_ERR_NONFINITE if any value is not
- * finite (out is still written). */
+ * runs give bit-identical values.  Pinned (mapped) host memory is written by
+ * the kernel itself, which saves a copy.  LB_ERR_NONFINITE if any value is
+ * not finite (out is still written). */
 int lb_pseudo_energy(lb_ctx* c, double out[6]);
 
 /* Copy up to cap trace rows (6 doubles each, same layout as

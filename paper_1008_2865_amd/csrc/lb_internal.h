@@ -132,6 +132,10 @@ hipError_t launch_step_batch(int storage, int mode, int tile_x, int rows_per_ite
                              int parity, uint32_t step, double* partials, hipStream_t s);
 hipError_t launch_final_batch(const BatchLattice* desc, int count, const double* partials,
                               double t, int64_t row, hipStream_t s);
+// Sets *flag (device memory or mapped host memory) to 1 if a value of v is not
+// finite or, with positive, not > 0; the flag is otherwise left alone.
+hipError_t launch_check(const double* v, int64_t n, bool positive, int* flag, hipStream_t s);
+hipError_t launch_clear(int* flag, hipStream_t s);
 hipError_t launch_moments(int storage, const void* src, const Geom& g,
                           const Coef& c, double* rho, double* ux, double* uy,
                           hipStream_t s);

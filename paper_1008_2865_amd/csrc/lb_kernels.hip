@@ -22,6 +22,7 @@
 // used, so results are bit-reproducible for a given launch shape.
 #include "lb_site.h"
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -738,6 +739,21 @@ k_final_batch(const BatchLattice* __restrict__ desc, const double* __restrict__ 
               d.trace + row * 6);
 }
 
+// Sets *flag to 1 if some value is not finite or, with positive, not > 0.  The
+// flag is only ever set, so no order of the stores matters.
+__global__ void __launch_bounds__(256)
+k_check(const double* __restrict__ v, int64_t n, bool positive, int* __restrict__ flag)
+{
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double x = v[i];
+        bad = bad || !(fabs(x) <= 1.7976931348623157e308) || (positive && !(x > 0.0));
+    }
+    if (bad) *flag = 1;
+}
+
+__global__ void k_clear(int* __restrict__ flag) { *flag = 0; }
+
 // rho and u = j / rho of the pre-collision state, dense [ny][nx] doubles.
 template <class P>
 __global__ void __launch_bounds__(256)
@@ -1046,6 +1062,19 @@ hipError_t launch_final(const double* partials, int blocks, double t,
                         double half_A1, double* out_row, hipStream_t s)
 {
     hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partials, blocks, t, half_A1, out_row);
+    return hipGetLastError();
+}
+
+hipError_t launch_check(const double* v, int64_t n, bool positive, int* flag, hipStream_t s)
+{
+    const int blocks = (int)std::min<int64_t>(2048, (n + 255) / 256);
+    hipLaunchKernelGGL(k_check, dim3(blocks), dim3(256), 0, s, v, n, positive, flag);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(int* flag, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, s, flag);
     return hipGetLastError();
 }
 

@@ -84,9 +84,11 @@ class LBSim:
 
     def pseudo_energy(self):
         """{t, M, E_s, E_m, sum psi^2, E_bulk} of the state at t."""
-        out = np.empty(6, np.float64)
-        B.lb_pseudo_energy(self.ctx, out)
-        return out
+        if getattr(self, "_row", None) is None:
+            # Pinned, so that the library's last kernel stores the row here.
+            self._row = self.torch.empty(6, dtype=self.torch.float64, pin_memory=True)
+        B.lb_pseudo_energy(self.ctx, self._row)
+        return self._row.numpy().copy()
 
     def structure_factor(self, spectrum=False):
         """(S_n, counts, kbar, R) of the density at t (square lattices; see
