@@ -197,8 +197,8 @@ const char* lb_last_error(void);
 /* ---------------------------------------------------------------------------
  * Batches: many independent periodic lattices, each with its own size,
  * couplings and initial density, advanced together by one kernel launch
- * per time step, or per two plain steps under the same rule as
- * lb_params.steps_per_launch (the step of every lattice is exactly the one
+ * per time step, or per several plain steps under the same rule as
+ * lb_params.steps_per_launch, whatever the launch shape (the step of every lattice is exactly the one
  * lb_step performs, so its fields are bit-identical to a lb_step run of the
  * same lattice).
  * ------------------------------------------------------------------------ */
@@ -239,8 +239,8 @@ int lb_batch_use_graphs(lb_batch* b, int enable);
 int lb_batch_two_step_shape(lb_batch* b, int32_t* tile_x, int32_t* tile_y, int32_t* blocks);
 
 /* Rows per workgroup of the batch's two-step launches: tile_y in [8, 64], or
- * 0 for the library's choice (the tallest of 48, 32, 24, 16 rows giving at
- * least 1400 workgroups).  Only the launch shape changes: fields stay
+ * 0 for the library's choice (the height of least rounds of resident
+ * workgroups times rows walked).  Only the launch shape changes: fields stay
  * bit-identical.  Synchronises the stream and drops captured graphs.
  * LB_ERR_STATE if the batch runs one step per launch. */
 int lb_batch_two_step_tile(lb_batch* b, int32_t tile_y);

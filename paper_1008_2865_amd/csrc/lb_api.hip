@@ -307,6 +307,51 @@ TileSplit split_tiles(int nx, int ny, int w, int h, int least, int64_t slots, in
     return s;
 }
 
+// Threads of the tiles of N sites, workgroups resident at once, most steps per
+// launch, and the widest and tallest tile for k steps.
+struct TileClass {
+    bool large;  // double precision: two workgroups of 256 threads per CU
+    int threads, steps;
+    int64_t slots;
+    TileClass(int64_t N, bool f64)
+    {
+        const bool round = N <= 256 * 34 * 36;  // one tile per CU
+        const int64_t area = (N + 255) / 256;
+        large = f64 && N > 1050000;
+        threads = large ? 256 : f64 || round ? 1024 : 512;
+        slots = !large && (f64 || round) ? 256 : 512;
+        steps = area <= 24 ? 5 : area <= 112 ? 4 : large ? 2 : 3;
+    }
+    int width(int k) const { return large ? 24 : lbk::kTilePitch - 6 * k + 2; }
+    int height(int k) const { return large ? 26 : lbk::kTileRows - 6 * k + 2; }
+};
+
+// The geometry of tiles of tx x ty sites (steps left open).
+lbk::TileGeom tile_geom(const lb_params& p, const Geom& g, int tx, int ty, int threads)
+{
+    lbk::TileGeom t{};
+    t.nx = p.nx;
+    t.ny = p.ny;
+    t.pitch = g.pitch;
+    t.plane = g.plane;
+    t.tx = tx;
+    t.ty = ty;
+    t.tiles_x = (p.nx + tx - 1) / tx;
+    t.tiles = t.tiles_x * ((p.ny + ty - 1) / ty);
+    t.threads = threads;
+    for (int j = 0; j < lbk::kTileMaxSteps; ++j) {
+        const uint32_t w = tx + 6 * j + 4;
+        t.magic[j] = (uint32_t)(((uint64_t(1) << 32) + w - 1) / w);
+    }
+    return t;
+}
+
+// Whether 32-bit byte offsets reach all of a plane.
+bool plane_fits(const lb_params& p, const Geom& g)
+{
+    return (uint64_t)g.plane * lbk::storage_bytes(p.storage) < (uint64_t(1) << 32);
+}
+
 // Plain steps of several levels per launch (lb_tile.hip), for lattices that
 // do not run two per launch in the row walk.
 struct TilePlan {
@@ -333,36 +378,19 @@ TilePlan make_tile(const lb_params& p, const Geom& g, bool two)
 {
     TilePlan t{};
     const int64_t N = (int64_t)p.nx * p.ny;
-    if (two || p.steps_per_launch != 0 || p.tile_x || p.tile_y || p.tile_rows ||
-        (uint64_t)g.plane * lbk::storage_bytes(p.storage) >= (uint64_t(1) << 32))
-        return t;
-    const bool f64 = p.storage == LB_F64, large = f64 && N > 1050000;
-    const bool round = N <= 256 * 34 * 36;  // one tile per CU
-    const int64_t slots = !large && (f64 || round) ? 256 : 512;
-    const int64_t area = (N + 255) / 256;
-    t.g.nx = p.nx;
-    t.g.ny = p.ny;
-    t.g.pitch = g.pitch;
-    t.g.plane = g.plane;
-    t.g.threads = large ? 256 : f64 || round ? 1024 : 512;
+    if (two || p.steps_per_launch != 0 || p.tile_x || p.tile_y || p.tile_rows || !plane_fits(p, g)) return t;
+    const TileClass c(N, p.storage == LB_F64);
     t.single = N <= 900000;
-    for (int k = area <= 24 ? 5 : area <= 112 ? 4 : large ? 2 : 3; k >= 1; --k) {
-        // Widest and tallest tile: within the region, and within one wrap
-        // of the lattice.
-        const int w = std::min(large ? 24 : lbk::kTilePitch - 6 * k + 2, p.nx - 3 * k + 2);
-        const int h = std::min(large ? 26 : lbk::kTileRows - 6 * k + 2, p.ny - 3 * k + 2);
+    for (int k = c.steps; k >= 1; --k) {
+        const int w = std::min(c.width(k), p.nx - 3 * k + 2), h = std::min(c.height(k), p.ny - 3 * k + 2);
         if (w < 4 || h < 4) continue;
-        if (k == 3 && !large &&
-            round_tiles(p.nx, p.ny, w, h, slots) >
-                round_tiles(p.nx, p.ny, lbk::kTilePitch - 10, lbk::kTileRows - 10, slots))
+        if (k == 3 && !c.large &&
+            round_tiles(p.nx, p.ny, w, h, c.slots) > round_tiles(p.nx, p.ny, c.width(2), c.height(2), c.slots))
             continue;  // three steps only where they need no more rounds than two
-        const TileSplit s = split_tiles(p.nx, p.ny, w, h, 4, slots, 6 * k - 2);
+        const TileSplit s = split_tiles(p.nx, p.ny, w, h, 4, c.slots, 6 * k - 2);
         if (!s.tx) continue;
         t.steps = k;
-        t.g.tx = s.tx;
-        t.g.ty = s.ty;
-        t.g.tiles_x = (p.nx + t.g.tx - 1) / t.g.tx;
-        t.g.tiles = t.g.tiles_x * ((p.ny + t.g.ty - 1) / t.g.ty);
+        t.g = tile_geom(p, g, s.tx, s.ty, c.threads);
         return t;
     }
     return t;
@@ -373,10 +401,6 @@ lbk::TileGeom tile_launch(const TilePlan& t, int steps)
 {
     lbk::TileGeom g = t.g;
     g.steps = steps;
-    for (int j = 0; j < steps; ++j) {
-        const uint32_t w = g.tx + 6 * (steps - 1 - j) + 4;
-        g.magic[j] = (uint32_t)(((uint64_t(1) << 32) + w - 1) / w);
-    }
     return g;
 }
 
@@ -446,6 +470,8 @@ struct lb_batch {
     lbk::BatchLattice* desc;   // device
     int32_t* tile_lattice;     // device
     int32_t* tile_lattice2;    // device, two-step tiles (when two)
+    lbk::TileBatch tile;       // tiles of several steps per launch
+    int tile_steps;            // most of their steps; 0: not used
     double* partials;          // device, 4 per tile
     int tiles, tiles2;
     bool two;                  // plain steps run two per launch
@@ -948,10 +974,61 @@ int check_batch(lb_batch* b)
     return LB_OK;
 }
 
+// Tiles of several steps per launch for a batch that does not run two in the
+// row walk: the smallest tile, shared by the lattices as far as their own
+// sizes allow, whose count fills no more rounds than the largest would.
+struct BatchTiles {
+    int steps, tx, ty, threads, tiles;
+    std::vector<lbk::TileGeom> geom;
+};
+
+void batch_tiles(const lb_params* ps, int32_t count, BatchTiles& t)
+{
+    int64_t N = 0;
+    int least = INT32_MAX;
+    for (int32_t i = 0; i < count; ++i) {
+        N += (int64_t)ps[i].nx * ps[i].ny;
+        least = std::min({least, ps[i].nx, ps[i].ny});
+        if (!plane_fits(ps[i], make_geom(ps[i]))) return;
+    }
+    const TileClass c(N, ps[0].storage == LB_F64);
+    auto tiles = [&](int k, int w, int h) {
+        int64_t n = 0;
+        for (int32_t i = 0; i < count; ++i) {
+            const int a = std::min(w, ps[i].nx - 3 * k + 2), b = std::min(h, ps[i].ny - 3 * k + 2);
+            n += (int64_t)((ps[i].nx + a - 1) / a) * ((ps[i].ny + b - 1) / b);
+        }
+        return n;
+    };
+    auto rounds = [&](int64_t n) { return (n + c.slots - 1) / c.slots; };
+    for (int k = c.steps; k >= 1; --k) {
+        if (least - 3 * k + 2 < 4) continue;
+        const int w = c.width(k), h = c.height(k);
+        const int64_t most = rounds(tiles(k, w, h));
+        if (k == 3 && !c.large && most > rounds(tiles(2, c.width(2), c.height(2)))) continue;
+        int side = w;
+        while (side > 4 && rounds(tiles(k, side - 1, std::min(h, side - 1))) <= most) --side;
+        if (tiles(k, side, std::min(h, side)) >= (int64_t(1) << 30)) return;
+        t.steps = k;
+        t.threads = c.threads;
+        for (int32_t i = 0; i < count; ++i) {
+            const int a = std::min(side, ps[i].nx - 3 * k + 2), b = std::min({side, h, ps[i].ny - 3 * k + 2});
+            const int na = (ps[i].nx + a - 1) / a, nb = (ps[i].ny + b - 1) / b;
+            t.geom.push_back(tile_geom(ps[i], make_geom(ps[i]), (ps[i].nx + na - 1) / na, (ps[i].ny + nb - 1) / nb,
+                                       c.threads));
+            t.tiles += t.geom.back().tiles;
+            t.tx = std::max(t.tx, t.geom.back().tx);
+            t.ty = std::max(t.ty, t.geom.back().ty);
+        }
+        return;
+    }
+}
+
 // Workspace of a batch: descriptor table, tile -> lattice table, partials,
 // then one single-lattice workspace per member.
 struct BatchLayout {
-    size_t desc, tile_lattice, tile_lattice2, partials;
+    size_t desc, tile_lattice, tile_lattice2, tile_lattice3, partials;
+    BatchTiles tile;
     std::vector<size_t> member, member_bytes;
     size_t total;
     int tiles, tiles2, tiles2_cap, tile_y2;
@@ -974,8 +1051,39 @@ Geom batch_geom2(const lb_params& p, int tile_y2)
     return make_geom2(q, make_geom(q));
 }
 
+// Height of the two-step tiles of a batch (128 lanes: the lattices of a batch
+// are narrow).  A workgroup walks its height and 7 rows more; a round of
+// resident workgroups takes about as long per row whether it is full or half
+// empty (single precision, full: 1.1 times; taken higher, the rule gives up
+// workgroups in flight that several batches at once would use).  So the height
+// is the one of least rounds x rows.
+// Measured us/step, 20 lattices of 9.2 million sites, FP32: 48 rows (1776
+// workgroups, 1.2 rounds of 1536) 113, 28 (2.0) 92.9, 60 (0.95) 91.5, 64 (0.85)
+// 93.4, 20 (2.8) 96.3; half storage 48 103, 60 73.6, 28 77.2.  13 lattices of 4.9
+// million: FP32 24 (1.2) 63.2, 32 (0.9) 51.4; half storage 60.2, 42.6.
+int batch_height2(const lb_params* ps, int32_t count)
+{
+    const int64_t slots = step2_slots(ps[0].storage, 128);
+    const double full = ps[0].storage == LB_F32 ? 1.1 : 1.05;
+    int best = kBatchMinTile2;
+    double least = 0.0;
+    for (int h = kBatchMinTile2; h <= kBatchMaxTile2; ++h) {
+        int64_t tiles = 0;
+        for (int32_t i = 0; i < count; ++i) tiles += batch_geom2(ps[i], h).blocks;
+        const int64_t rounds = tiles / slots, rest = tiles % slots;
+        const double cost = (h + 7) * (full * (double)rounds +
+                                       (rest ? std::max(1.0, full * (double)rest / (double)slots) : 0.0));
+        if (h == kBatchMinTile2 || cost < least) {
+            least = cost;
+            best = h;
+        }
+    }
+    return best;
+}
+
 int batch_layout(const lb_params* ps, int32_t count, BatchLayout* L)
 {
+    L->tile = BatchTiles{};
     if (!ps) return fail(LB_ERR_INVALID, "params is NULL");
     if (count < 1 || count > 65536) return fail(LB_ERR_INVALID, "count must be in [1, 65536]");
     int rc;
@@ -999,23 +1107,17 @@ int batch_layout(const lb_params* ps, int32_t count, BatchLayout* L)
             return fail(LB_ERR_INVALID, "too many tiles in the batch");
         L->tiles += g.blocks;
     }
-    // Two steps per launch: FP32 or half storage, by default when the batch
-    // as a whole fills tiles of >= 16 rows (the tallest of 48, 32, 24, 16
-    // rows giving >= 1400 workgroups of 128 lanes; the lattices of a batch
-    // are narrow, so the tiles stay 128 lanes wide).
+    // Two steps per launch in the row walk: FP32 or half storage, by default
+    // for 1.9 million sites and more.  Below that the tiles of batch_tiles are
+    // faster: FP32 us/step, 0.72 million sites 11.1 against 14.6, 1.57 million
+    // 19.4 against 21.1, 1.97 million 23.9 against 24.4, 2.4 million 29.4
+    // against 27.7 (one step per launch 36 at 1.8 million).
     const int spl = ps[0].steps_per_launch;
-    int tile_y2 = 0;
-    for (int r : {48, 32, 24, 16}) {
-        int64_t blocks = 0;
-        for (int32_t i = 0; i < count; ++i) blocks += batch_geom2(ps[i], r).blocks;
-        if (blocks >= 1400 && blocks < (int64_t(1) << 30)) {
-            tile_y2 = r;
-            break;
-        }
-    }
     const int st = ps[0].storage;
-    L->two = (st == LB_F32 || st == LB_F16DEV) && (spl == 2 || (spl == 0 && tile_y2 >= 16));
-    if (L->two && tile_y2 == 0) tile_y2 = 8;
+    int64_t sites = 0;
+    for (int32_t i = 0; i < count; ++i) sites += (int64_t)ps[i].nx * ps[i].ny;
+    L->two = (st == LB_F32 || st == LB_F16DEV) && (spl == 2 || (spl == 0 && sites >= 1900000));
+    const int tile_y2 = L->two ? batch_height2(ps, count) : 0;
     L->tile_y2 = L->two ? tile_y2 : 0;
     L->tiles2 = 0;
     L->tiles2_cap = 0;
@@ -1035,6 +1137,9 @@ int batch_layout(const lb_params* ps, int32_t count, BatchLayout* L)
     off += align_up(sizeof(int32_t) * L->tiles);
     L->tile_lattice2 = off;
     off += align_up(sizeof(int32_t) * L->tiles2_cap);
+    if (spl == 0 && !L->two) batch_tiles(ps, count, L->tile);
+    L->tile_lattice3 = off;
+    off += align_up(sizeof(int32_t) * L->tile.tiles);
     L->partials = off;
     off += align_up(sizeof(double) * 4 * L->tiles);
     L->member.resize(count);
@@ -1057,30 +1162,44 @@ hipError_t batch_launch(lb_batch* b, int mode, int parity, int64_t t)
                                   b->stream);
 }
 
-// Buffer flips of a run of n plain steps: one per launch.
-int batch_flips(const lb_batch* b, int64_t n)
+// Steps of the next launch of a run of n plain steps.
+int batch_steps(const lb_batch* b, int64_t n)
 {
-    return (int)((b->two ? n / 2 + (n & 1) : n) & 1);
+    if (b->tile_steps) return even_steps(n, b->tile_steps);
+    return b->two && n > 1 ? 2 : 1;
 }
 
-// n plain steps from buf[parity] at time t, launch by launch: pairs in the
-// two-step kernel when the batch runs them so, then any odd step.  *done
+// Buffer flips of the first m steps of a run of n plain steps: one per launch.
+int batch_flips(const lb_batch* b, int64_t n, int64_t m)
+{
+    int flips = 0;
+    for (int64_t j = 0; j < m; ++flips) j += batch_steps(b, n - j);
+    return flips & 1;
+}
+
+// n plain steps from buf[parity] at time t, launch by launch: on tiles, or
+// pairs in the two-step kernel and then any odd step, or one by one.  *done
 // counts the steps whose launch was issued (all n unless one fails).
 hipError_t batch_run(lb_batch* b, int64_t n, int parity, int64_t t, int64_t* done)
 {
-    int64_t j = 0;
-    *done = 0;
-    if (b->two)
-        for (; j + 1 < n; j += 2, parity ^= 1) {
-            hipError_t e = lbk::launch_step2_batch(b->storage, b->tile_x2, b->desc, b->tile_lattice2,
-                                                   b->tiles2, parity, (uint32_t)(t + j), b->stream);
-            if (e != hipSuccess) return e;
-            *done = j + 2;
+    for (*done = 0; *done < n; parity ^= 1) {
+        const int k = batch_steps(b, n - *done);
+        const int64_t now = t + *done;
+        hipError_t e;
+        if (b->tile_steps) {
+            lbk::TileBatch launch = b->tile;
+            launch.parity = parity;
+            launch.steps = k;
+            launch.step = (uint32_t)now;
+            e = lbk::launch_tile_batch(b->storage, launch, b->stream);
+        } else if (k == 2) {
+            e = lbk::launch_step2_batch(b->storage, b->tile_x2, b->desc, b->tile_lattice2, b->tiles2, parity,
+                                        (uint32_t)now, b->stream);
+        } else {
+            e = batch_launch(b, lbk::MODE_STEP, parity, now);
         }
-    for (; j < n; ++j, parity ^= 1) {
-        hipError_t e = batch_launch(b, lbk::MODE_STEP, parity, t + j);
         if (e != hipSuccess) return e;
-        *done = j + 1;
+        *done += k;
     }
     return hipSuccess;
 }
@@ -1163,8 +1282,7 @@ int batch_advance(lb_batch* b, int64_t n)
         }
         int64_t issued = 0;
         hipError_t e = batch_plain(b, run, &issued);
-        // Launches issued: pairs first, then any odd step (as batch_run).
-        b->parity ^= batch_flips(b, issued);
+        b->parity ^= batch_flips(b, run, issued);
         b->t += issued;
         done += issued;
         if (e) return hip_fail(e, "batched step launch");
@@ -1214,7 +1332,8 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     lb_batch* b = new lb_batch();
     b->stream = static_cast<hipStream_t>(hip_stream);
     std::vector<lbk::BatchLattice> desc(count);
-    std::vector<int32_t> tl(L.tiles), tl2(L.tiles2);
+    std::vector<int32_t> tl(L.tiles), tl2(L.tiles2), tl3;
+    tl3.reserve(L.tile.tiles);
     int tile = 0, tile2 = 0;
     for (int32_t i = 0; i < count; ++i) {
         lb_ctx* c = nullptr;
@@ -1232,7 +1351,7 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
         c->batch = b;
         b->members.push_back(c);
         lbk::BatchLattice& d = desc[i];
-        std::memset(&d, 0, sizeof d);
+        std::memset(static_cast<void*>(&d), 0, sizeof d);
         d.geom = c->g;
         d.coef = c->coef;
         lbk::coef_to_f32(c->coef, d.coef_f);
@@ -1249,11 +1368,24 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
             for (int j = 0; j < d.geom2.blocks; ++j) tl2[tile2 + j] = i;
             tile2 += d.geom2.blocks;
         }
+        if (L.tile.steps) {
+            d.tile = L.tile.geom[i];
+            d.tile_begin3 = (int32_t)tl3.size();
+            tl3.insert(tl3.end(), d.tile.tiles, i);
+        }
     }
     lb_ctx* c0 = b->members[0];
     b->desc = reinterpret_cast<lbk::BatchLattice*>(ws + L.desc);
     b->tile_lattice = reinterpret_cast<int32_t*>(ws + L.tile_lattice);
     b->tile_lattice2 = reinterpret_cast<int32_t*>(ws + L.tile_lattice2);
+    b->tile = lbk::TileBatch{};
+    b->tile.desc = b->desc;
+    b->tile.tile_lattice = reinterpret_cast<int32_t*>(ws + L.tile_lattice3);
+    b->tile.tiles = L.tile.tiles;
+    b->tile.tx = L.tile.tx;
+    b->tile.ty = L.tile.ty;
+    b->tile.threads = L.tile.threads;
+    b->tile_steps = L.tile.steps;
     b->partials = reinterpret_cast<double*>(ws + L.partials);
     b->tiles = L.tiles;
     b->tiles2 = L.tiles2;
@@ -1283,6 +1415,9 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     if (!e && L.tiles2)
         e = hipMemcpyAsync(b->tile_lattice2, tl2.data(), sizeof(int32_t) * L.tiles2,
                            hipMemcpyHostToDevice, b->stream);
+    if (!e && !tl3.empty())
+        e = hipMemcpyAsync(ws + L.tile_lattice3, tl3.data(), sizeof(int32_t) * tl3.size(), hipMemcpyHostToDevice,
+                           b->stream);
     if (!e) e = hipStreamSynchronize(b->stream);
     if (e) {
         for (lb_ctx* m : b->members) {

@@ -64,6 +64,20 @@ struct Coef {
     uint32_t step;              // time step of the launch
 };
 
+// Several plain steps in one launch (lb_tile.hip): tiles of tx x ty sites,
+// whose region of the first step, tx + 6 steps - 2 by ty + 6 steps - 2
+// sites, fits kTilePitch x kTileRows and wraps around the lattice at most
+// once.  A population plane spans less than 2^32 bytes.  With a tape (F64 and
+// F32 only), step j also writes the tape entry of the state it leaves to
+// tape + 4 j nx ny.
+constexpr int kTilePitch = 44, kTileRows = 46, kTileMaxSteps = 5;
+struct TileGeom {
+    int32_t nx, ny, pitch;
+    int64_t plane;
+    int32_t tx, ty, tiles_x, tiles, threads;
+    int32_t steps;                  // of this launch
+    uint32_t magic[kTileMaxSteps];  // division by the region's width, by steps left after it
+};
 // One lattice of a batch, as the batched kernels read it (device memory).
 struct BatchLattice {
     Geom geom;
@@ -74,9 +88,10 @@ struct BatchLattice {
     double half_A1;      // (G1 + G2) / 2
     int32_t tile_begin;  // first logical tile of this lattice in the batch
     int32_t tile_begin2; // first logical tile of this lattice in the two-step tile list
+    int32_t tile_begin3; // first tile of this lattice in the list of lb_tile.hip's tiles
     float coef_f[13];    // coef converted to single precision (coef_to_f32), so the
                          // single-precision kernels read it without converting
-    int32_t pad;
+    TileGeom tile;       // tiles of several steps per launch (when the batch runs them)
 };
 
 // coef in single precision, exactly as the single-lattice launchers pass it:
@@ -109,22 +124,17 @@ hipError_t launch_step2_batch(int storage, int tile_x, const BatchLattice* desc,
 // kernel's registers and LDS, per compute unit, times the compute units.
 // -1 when no device can be asked.
 int step2_resident(int storage, int tile_x);
-// Several plain steps in one launch (lb_tile.hip): tiles of tx x ty sites,
-// whose region of the first step, tx + 6 steps - 2 by ty + 6 steps - 2
-// sites, fits kTilePitch x kTileRows and wraps around the lattice at most
-// once.  A population plane spans less than 2^32 bytes.  With a tape (F64 and
-// F32 only), step j also writes the tape entry of the state it leaves to
-// tape + 4 j nx ny.
-constexpr int kTilePitch = 44, kTileRows = 46, kTileMaxSteps = 5;
-struct TileGeom {
-    int32_t nx, ny, pitch;
-    int64_t plane;
-    int32_t tx, ty, tiles_x, tiles, threads;
-    int32_t steps;                  // of this launch
-    uint32_t magic[kTileMaxSteps];  // division by the region's width, by step
-};
 hipError_t launch_tile(int storage, const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape,
                        hipStream_t s);
+// The same for every lattice of a batch, whose tiles have at most tx x ty sites.
+struct TileBatch {
+    const BatchLattice* desc;
+    const int32_t* tile_lattice;  // lattice of each tile
+    int tiles, tx, ty, threads;
+    int parity, steps;            // reads buf[parity], writes buf[parity ^ 1]
+    uint32_t step;                // time level of the first step
+};
+hipError_t launch_tile_batch(int storage, const TileBatch& b, hipStream_t s);
 hipError_t launch_final(const double* partials, int blocks, double t,
                         double half_A1, double* out_row, hipStream_t s);
 hipError_t launch_step_batch(int storage, int mode, int tile_x, int rows_per_iter, int min_tile_y,

@@ -24,6 +24,8 @@
 // 1200^2 44 -> 33, 2048^2 128 -> 98.
 #include "lb_site.h"
 
+#include <type_traits>
+
 namespace lbk {
 namespace {
 
@@ -35,10 +37,11 @@ __device__ __forceinline__ const T* at32(const T* base, int e)
     return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)e * (uint32_t)sizeof(T));
 }
 
+// Tile lb of a lattice.
 template <class P, int NT, int kPitch, int kRows, bool kTape>
-__global__ void __launch_bounds__(NT)
-k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, TileGeom g,
-       CoefT<typename P::C> k, typename P::C* __restrict__ tape)
+__device__ __forceinline__ void
+tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, const TileGeom& g, const int steps,
+           const CoefT<typename P::C>& k, typename P::C* __restrict__ tape, const int lb)
 {
     using S = typename P::S;
     using C = typename P::C;
@@ -50,7 +53,6 @@ k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, T
     S* const post = reinterpret_cast<S*>(psi + kPitch * kRows);
 
     const int tid = threadIdx.x;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
     const int sy = lb / g.tiles_x;
     const int x0 = (lb - sy * g.tiles_x) * g.tx, y0 = sy * g.ty;
     const int nx = g.nx, ny = g.ny;
@@ -66,12 +68,12 @@ k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, T
     }
 
 #pragma unroll 1
-    for (int j = 0; j < g.steps; ++j) {
+    for (int j = 0; j < steps; ++j) {
         // Sites in reach of this step: the tile and `halo` more on each side,
         // 3 j in from the first step's region.
-        const int halo = 3 * (g.steps - 1 - j) + 2, in = 3 * j;
+        const int halo = 3 * (steps - 1 - j) + 2, in = 3 * j;
         const int w = g.tx + 2 * halo, h = g.ty + 2 * halo, ns = w * h;
-        const uint32_t magic = g.magic[j];
+        const uint32_t magic = g.magic[steps - 1 - j];
         // Site i of this thread; past the end the last site again (the same
         // values written twice), so that no load is conditional.
         auto site = [&](int i, int& x, int& y) {
@@ -114,7 +116,7 @@ k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, T
         }
         __syncthreads();
 
-        const bool last = j + 1 == g.steps;
+        const bool last = j + 1 == steps;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             if (i * NT >= ns) break;
@@ -142,6 +144,46 @@ k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, T
     }
 }
 
+template <class P, int NT, int kPitch, int kRows, bool kTape>
+__global__ void __launch_bounds__(NT)
+k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, TileGeom g,
+       CoefT<typename P::C> k, typename P::C* __restrict__ tape)
+{
+    tile_steps<P, NT, kPitch, kRows, kTape>(src, dst, g, g.steps, k, tape, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+// The same for every lattice of a batch: the tiles of all lattices are
+// numbered consecutively, tile_lattice gives a tile's lattice.
+template <class P, int NT, int kPitch, int kRows>
+__global__ void __launch_bounds__(NT)
+k_tile_batch(const BatchLattice* __restrict__ desc, const int32_t* __restrict__ tile_lattice, int parity,
+             uint32_t step, int steps)
+{
+    using S = typename P::S;
+    const int gl = xcd_remap(blockIdx.x, gridDim.x);
+    const BatchLattice& d = desc[tile_lattice[gl]];
+    CoefT<typename P::C> k;
+    if constexpr (sizeof(typename P::C) == 4) {
+        const float* c = d.coef_f;
+        k = CoefT<float>{c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9], c[10], c[11], c[12], step};
+    } else {
+        k = convert<double>(d.coef);
+        k.step = step;
+    }
+    tile_steps<P, NT, kPitch, kRows, false>(static_cast<const S*>(d.buf[parity]),
+                                            static_cast<S*>(d.buf[parity ^ 1]), d.tile, steps, k, nullptr,
+                                            gl - d.tile_begin3);
+}
+
+// LDS of a launch: psi, and with more than one step the post-collision planes.
+template <class P, int kPitch, int kRows>
+size_t tile_lds(int steps)
+{
+    constexpr size_t psi = sizeof(typename P::C) * kPitch * kRows;
+    constexpr size_t post = sizeof(typename P::S) * 9 * (kPitch - 4) * (kRows - 4);
+    return psi + (steps > 1 ? post : 0);
+}
+
 template <class P, int NT, int kPitch, int kRows>
 hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
 {
@@ -150,8 +192,7 @@ hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c,
     const auto k = convert<C>(c);
     const S* a = static_cast<const S*>(src);
     S* b = static_cast<S*>(dst);
-    constexpr size_t psi = sizeof(C) * kPitch * kRows, post = sizeof(S) * 9 * (kPitch - 4) * (kRows - 4);
-    const size_t lds = psi + (g.steps > 1 ? post : 0);
+    const size_t lds = tile_lds<P, kPitch, kRows>(g.steps);
     if (tape) {
         if constexpr (P::kDev)
             return hipErrorInvalidValue;
@@ -165,25 +206,56 @@ hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c,
     return hipGetLastError();
 }
 
+template <class P, int NT, int kPitch, int kRows>
+hipError_t batch_nt(const TileBatch& b, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_tile_batch<P, NT, kPitch, kRows>), dim3(b.tiles), dim3(NT),
+                       (tile_lds<P, kPitch, kRows>(b.steps)), s, b.desc, b.tile_lattice, b.parity, b.step, b.steps);
+    return hipGetLastError();
+}
+
+template <int W, int H>
+struct Region {
+    static constexpr int w = W, h = H;
+};
+
+// Calls fn with the threads and the region of tiles of tx x ty sites: 34 x 36
+// sites keep two double-precision workgroups on a CU, 44 x 46 one.
+template <class P, class Fn>
+hipError_t with_shape(int threads, int tx, int ty, int steps, Fn&& fn)
+{
+    const int w = tx + 6 * steps - 2, h = ty + 6 * steps - 2;
+    if (steps < 1 || steps > kTileMaxSteps || w > kTilePitch || h > kTileRows) return hipErrorInvalidValue;
+    using Small = Region<34, 36>;
+    using Large = Region<kTilePitch, kTileRows>;
+    const bool small = w <= 34 && h <= 36;
+    if (threads == 1024)
+        return small ? fn(std::integral_constant<int, 1024>{}, Small{})
+                     : fn(std::integral_constant<int, 1024>{}, Large{});
+    if constexpr (sizeof(typename P::C) == 8) {
+        if (threads == 256 && small) return fn(std::integral_constant<int, 256>{}, Small{});
+    } else {
+        if (threads == 512)
+            return small ? fn(std::integral_constant<int, 512>{}, Small{})
+                         : fn(std::integral_constant<int, 512>{}, Large{});
+    }
+    return hipErrorInvalidValue;
+}
+
 template <class P>
 hipError_t tile_p(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
 {
-    const int w = g.tx + 6 * g.steps - 2, h = g.ty + 6 * g.steps - 2;
-    if (g.steps < 1 || g.steps > kTileMaxSteps || w > kTilePitch || h > kTileRows) return hipErrorInvalidValue;
-    // The first step's region: 34 x 36 sites keep two double-precision
-    // workgroups on a CU, 44 x 46 one.
-    const bool small = w <= 34 && h <= 36;
-    switch (g.threads) {
-    case 1024: return small ? tile_nt<P, 1024, 34, 36>(src, dst, g, c, tape, s)
-                            : tile_nt<P, 1024, kTilePitch, kTileRows>(src, dst, g, c, tape, s);
-    case 512: return small ? tile_nt<P, 512, 34, 36>(src, dst, g, c, tape, s)
-                           : tile_nt<P, 512, kTilePitch, kTileRows>(src, dst, g, c, tape, s);
-    case 256:
-        if constexpr (sizeof(typename P::C) == 8)
-            if (small) return tile_nt<P, 256, 34, 36>(src, dst, g, c, tape, s);
-        return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
-    }
+    return with_shape<P>(g.threads, g.tx, g.ty, g.steps, [&](auto nt, auto region) {
+        return tile_nt<P, nt.value, region.w, region.h>(src, dst, g, c, tape, s);
+    });
+}
+
+template <class P>
+hipError_t batch_p(const TileBatch& b, hipStream_t s)
+{
+    return with_shape<P>(b.threads, b.tx, b.ty, b.steps, [&](auto nt, auto region) {
+        return batch_nt<P, nt.value, region.w, region.h>(b, s);
+    });
 }
 
 }  // namespace
@@ -195,6 +267,17 @@ hipError_t launch_tile(int storage, const void* src, void* dst, const TileGeom& 
     case ST_F64: return tile_p<PF64>(src, dst, g, c, tape, s);
     case ST_F32: return tile_p<PF32>(src, dst, g, c, tape, s);
     case ST_F16DEV: return tile_p<PF16>(src, dst, g, c, tape, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_tile_batch(int storage, const TileBatch& b, hipStream_t s)
+{
+    if (b.tiles <= 0) return hipErrorInvalidValue;
+    switch (storage) {
+    case ST_F64: return batch_p<PF64>(b, s);
+    case ST_F32: return batch_p<PF32>(b, s);
+    case ST_F16DEV: return batch_p<PF16>(b, s);
     default: return hipErrorInvalidValue;
     }
 }
