@@ -162,8 +162,9 @@ Geom make_geom(const lb_params& p)
 // Explicit tile_x / tile_y apply to both kernels; the library's choice
 // follows.
 // Workgroups of the two-step kernel resident at once: the runtime's
-// occupancy query on the current device (registers and LDS of the kernel as
-// built) times its compute units.  Without a device to ask, the value for
+// occupancy query on the current device (registers and LDS of the kernel for
+// any tau as built; the one for tau = 1 needs fewer registers, but a fourth wave
+// per SIMD gains nothing) times its compute units.  Without a device to ask, the value for
 // the MI355X as the kernel is built today: 3 waves per SIMD, i.e. 6
 // workgroups of 128 lanes or 3 of 256 lanes per CU, on 256 CUs (a GPU test
 // holds this to the occupancy query).
@@ -259,17 +260,17 @@ Geom make_geom2(const lb_params& p, const Geom& g)
 }
 
 // Whether plain steps run two per launch: FP32 or half storage when asked
-// for (steps_per_launch = 2), and by default on lattices of 1.3 million sites
-// large enough for tiles of 8 rows or more (below that lb_tile.hip's kernel
-// is faster: FP32 1100^2 14.0 us/step against 15.9, half storage 14.2
-// against 17.0; 1200^2 16.3 against 15.8, 16.1 against 16.5).  Half storage, two per launch
-// against one: 2048^2 41.1 against 48.1 us/step, 4096^2 152.8 against
-// 166.3, 8192^2 551 against 627.
+// for (steps_per_launch = 2), and by default on lattices of 1.2 million sites
+// large enough for tiles of 8 rows or more.  Below that lb_tile.hip's kernel is
+// about as fast or faster (us/step against two per launch: 900^2 11.1 and 12.0 in
+// FP32, 12.3 and 12.6 in half storage; 1040^2 13.4 and 13.1, 13.6 and 13.9),
+// above it slower (1120^2 14.5 and 14.2, 15.7 and 14.5; 1140^2 16.1 and 14.2,
+// 16.3 and 14.5).
 bool use_two(const lb_params& p, const Geom& g2)
 {
     if (p.storage != LB_F32 && p.storage != LB_F16DEV) return false;
     if (p.steps_per_launch == 2) return true;
-    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (int64_t)p.nx * p.ny >= 1300000;
+    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (int64_t)p.nx * p.ny >= 1200000;
 }
 
 // Tiles of at most w x h sites that cover an nx x ny lattice, rounded up to
@@ -475,6 +476,7 @@ struct lb_batch {
     double* partials;          // device, 4 per tile
     int tiles, tiles2;
     bool two;                  // plain steps run two per launch
+    bool tau1;                 // tau is 1 in every lattice
     int tile_x2, tile_y2;
     int storage, tile_x, rows_per_iter, min_tile_y;
     int device;
@@ -1054,20 +1056,22 @@ Geom batch_geom2(const lb_params& p, int tile_y2)
 // Height of the two-step tiles of a batch (128 lanes: the lattices of a batch
 // are narrow).  A workgroup walks its height and 7 rows more; a round of
 // resident workgroups takes about as long per row whether it is full or half
-// empty (single precision, full: 1.1 times; taken higher, the rule gives up
-// workgroups in flight that several batches at once would use).  So the height
-// is the one of least rounds x rows.
-// Measured us/step, 20 lattices of 9.2 million sites, FP32: 48 rows (1776
-// workgroups, 1.2 rounds of 1536) 113, 28 (2.0) 92.9, 60 (0.95) 91.5, 64 (0.85)
-// 93.4, 20 (2.8) 96.3; half storage 48 103, 60 73.6, 28 77.2.  13 lattices of 4.9
-// million: FP32 24 (1.2) 63.2, 32 (0.9) 51.4; half storage 60.2, 42.6.
+// empty (single precision, full: 1.1 times).  So the height is the one of least
+// rounds x rows, in single precision up to 48 rows: taller tiles are faster for
+// a batch alone, slower for several at once.  Measured us/step, 20 lattices of
+// 9.2 million sites, FP32 (alone; three batches on three streams): 48 rows (1776
+// workgroups, 1.2 rounds of 1536) 106, 81.9; 28 (2.0) 91.0, 81.2; 60 (0.95) 85.0,
+// 83.6; 20 (2.8) 94.8, 82.6; half storage 48 88.8, 58.9, 28 69.2, 62.7, 60 64.9,
+// 57.8.  13 lattices of 4.9 million alone: FP32 24 (1.2) 57.8, 32 (0.9) 47.1; half
+// storage 51.0, 38.5.
 int batch_height2(const lb_params* ps, int32_t count)
 {
     const int64_t slots = step2_slots(ps[0].storage, 128);
     const double full = ps[0].storage == LB_F32 ? 1.1 : 1.05;
+    const int most = ps[0].storage == LB_F32 ? 48 : kBatchMaxTile2;
     int best = kBatchMinTile2;
     double least = 0.0;
-    for (int h = kBatchMinTile2; h <= kBatchMaxTile2; ++h) {
+    for (int h = kBatchMinTile2; h <= most; ++h) {
         int64_t tiles = 0;
         for (int32_t i = 0; i < count; ++i) tiles += batch_geom2(ps[i], h).blocks;
         const int64_t rounds = tiles / slots, rest = tiles % slots;
@@ -1108,15 +1112,15 @@ int batch_layout(const lb_params* ps, int32_t count, BatchLayout* L)
         L->tiles += g.blocks;
     }
     // Two steps per launch in the row walk: FP32 or half storage, by default
-    // for 1.9 million sites and more.  Below that the tiles of batch_tiles are
-    // faster: FP32 us/step, 0.72 million sites 11.1 against 14.6, 1.57 million
-    // 19.4 against 21.1, 1.97 million 23.9 against 24.4, 2.4 million 29.4
-    // against 27.7 (one step per launch 36 at 1.8 million).
+    // for a million sites and more.  Below that the tiles of batch_tiles are
+    // faster: us/step, 0.61 million sites 10.6 against 12.2 in FP32, 11.4 against
+    // 12.9 in half storage; 0.72 million 10.9 against 12.9, 12.1 against 13.8;
+    // 1.2 million 16.8 against 15.6, 17.6 against 16.8.
     const int spl = ps[0].steps_per_launch;
     const int st = ps[0].storage;
     int64_t sites = 0;
     for (int32_t i = 0; i < count; ++i) sites += (int64_t)ps[i].nx * ps[i].ny;
-    L->two = (st == LB_F32 || st == LB_F16DEV) && (spl == 2 || (spl == 0 && sites >= 1900000));
+    L->two = (st == LB_F32 || st == LB_F16DEV) && (spl == 2 || (spl == 0 && sites >= 1000000));
     const int tile_y2 = L->two ? batch_height2(ps, count) : 0;
     L->tile_y2 = L->two ? tile_y2 : 0;
     L->tiles2 = 0;
@@ -1193,7 +1197,7 @@ hipError_t batch_run(lb_batch* b, int64_t n, int parity, int64_t t, int64_t* don
             launch.step = (uint32_t)now;
             e = lbk::launch_tile_batch(b->storage, launch, b->stream);
         } else if (k == 2) {
-            e = lbk::launch_step2_batch(b->storage, b->tile_x2, b->desc, b->tile_lattice2, b->tiles2, parity,
+            e = lbk::launch_step2_batch(b->storage, b->tau1, b->tile_x2, b->desc, b->tile_lattice2, b->tiles2, parity,
                                         (uint32_t)now, b->stream);
         } else {
             e = batch_launch(b, lbk::MODE_STEP, parity, now);
@@ -1390,6 +1394,7 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     b->tiles = L.tiles;
     b->tiles2 = L.tiles2;
     b->two = L.two;
+    b->tau1 = std::all_of(ps, ps + count, [](const lb_params& p) { return 1.0 / p.tau == 1.0; });
     b->tile_x2 = 128;
     b->tile_y2 = L.tile_y2;
     b->storage = ps[0].storage;

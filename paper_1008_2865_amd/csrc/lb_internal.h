@@ -112,11 +112,12 @@ hipError_t launch_step(int storage, int mode, const void* src, void* dst,
 // ceil(nx / (tile_x - 6)), blocks = tiles_x * ceil(ny / tile_y).
 hipError_t launch_step2(int storage, const void* src, void* dst, const Geom& g, const Coef& c,
                         hipStream_t s);
-// Two plain steps of every lattice of a batch in one launch: tiles logical
+// Two plain steps of every lattice of a batch in one launch (tau1: tau is 1 in
+// every lattice): tiles logical
 // tiles of tile_x lanes, tile_lattice maps each to its lattice, whose geom2
 // gives the tile's place; the launch reads buf[parity] and writes
 // buf[parity ^ 1] of every lattice.
-hipError_t launch_step2_batch(int storage, int tile_x, const BatchLattice* desc,
+hipError_t launch_step2_batch(int storage, bool tau1, int tile_x, const BatchLattice* desc,
                               const int32_t* tile_lattice, int tiles, int parity, uint32_t step,
                               hipStream_t s);
 // Workgroups of tile_x lanes of the two-step kernel (ST_F32 or ST_F16DEV)

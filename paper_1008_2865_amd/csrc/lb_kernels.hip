@@ -244,7 +244,7 @@ step_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst
             }
 
             if (kCollide) {
-                site_collide<kTape, P::kDev>(R, st, k, q[m], tp[m], o.o1, o.o2);
+                site_collide<kTape, P::kDev>(R, moments(R), st, k, q[m], tp[m], o.o1, o.o2);
                 if (m == 0) anchor = q[m][1];
             } else if (m == 0) {
                 anchor = p;
@@ -338,8 +338,8 @@ step_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst
 
 // ---------------------------------------------------------------------------
 // Two time steps per launch (temporal blocking) for plain steps of the
-// single-precision and half storages.  A tile of NT lanes produces NT - 6 output columns x0 .. x0+W-1 of
-// step t+2 for tile_y rows.  Level 1 is the one-step row walk above on the
+// single-precision and half storages.  A tile of NT lanes produces NT - 6
+// output columns x0 .. x0+W-1 of step t+2 for tile_y rows.  Level 1 is the one-step row walk above on the
 // NT columns x0-3 .. x0+NT-4 and on rows -3 .. nrows+2 of the tile (walk
 // order); its post-collision rows go to a 4-row LDS ring instead of memory.
 // Level 2 trails it: at walk row p it pulls the pre-collision populations of
@@ -352,17 +352,37 @@ step_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst
 // rings are deep enough).  Global traffic per two steps is one read and one
 // write of the populations, plus halo rows and columns that neighbouring
 // tiles also read.
+//
+// Neighbouring tiles walk in opposite directions, so that they reach a shared
+// halo together, and every tile turns round from one launch to the next: the
+// rows a launch wrote last are read first while the memory-side cache holds them
+// (FP32 3000^2 80.5 -> 73.7 us per step, 4096^2 141.5 -> 136.1; reversing the
+// order of the tiles as well gains nothing).
+//
+// What bounds it: single precision, memory (2048^2 79 us per launch whether 6 or
+// 3 workgroups are resident on a CU, 4.4 TB/s of fabric traffic); half storage,
+// the vector ALU and the latency of a row.  So a row's loads are issued before
+// all else and waited for after the row's arithmetic, slots are constants, only
+// three moments of a waiting row are kept at tau = 1, addresses are a uniform
+// base and a 32-bit lane offset, and a halo column's density is summed by lane
+// shifts.  us per step before and after all of these and the turning: FP32
+// 2048^2 40.0 -> 38.9, 3000^2 80.3 -> 72.7, 4096^2 141.2 -> 136.5; half storage
+// 2048^2 31.2 -> 27.4, 4096^2 (tau 0.8) 116.5 -> 102, 8192^2 416 -> 362.
 // ---------------------------------------------------------------------------
 // LDS of a two-step workgroup, declared once per kernel so that the walks
-// for tau = 1 and for other tau share it.
+// for tau = 1 and for other tau share it.  The rings are powers of two and
+// the walk is unrolled by their length, so that every slot is a constant.  At
+// 128 lanes in single precision that is 26880 bytes: six workgroups fit on a CU.
 template <class P, int NT>
 struct Step2Smem {
-    static constexpr int RS = 6, RS2 = 6, NF = 4;
-    typename P::C ring[RS][NT + 4];   // psi at t, level-1 rows p-2 .. p+3
-    typename P::C ring2[RS2][NT + 4]; // psi at t+1, rows p-7 .. p-2
+    static constexpr int U = 8, NF = 4;
+    // fs lies between the rings: lanes -1 and NT of its first and last row,
+    // which lanes 0 and NT - 1 read for values no output uses, are there.
+    typename P::C ring[U][NT + 4];  // psi at t: level-1 row r in slot r + 5
     // Post-collision populations of step t+1, in the storage type and
-    // rounded exactly as a one-step launch stores them.
+    // rounded exactly as a one-step launch stores them: row r in slot r + 4.
     typename P::S fs[NF][9][NT];
+    typename P::C ring2[U][NT + 4];  // psi at t+1: row r in slot r + 5
 };
 
 // Issue priority of a wave for one walk row.  Among waves of equal
@@ -384,6 +404,21 @@ __device__ __forceinline__ void set_row_priority(int it)
     }
 }
 
+// Rows a two-step walk loads ahead of the row it stages: in half storage, whose
+// walk waits for latency and the vector ALU, two (8192^2: 372 us per step
+// against 391 with one); in single precision, which is near the memory's rate,
+// one (4096^2: 136.8 against 142.8).
+template <class P>
+constexpr int kStep2Lead = P::kDev ? 2 : 1;
+
+// The value of another lane of the same 16: 0xB1 swaps the lanes of each
+// pair, 0x100 + n takes it from n lanes up.
+template <int kCtrl>
+__device__ __forceinline__ float row_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+
 template <class P, int NT, int kOm>
 __device__ __forceinline__ void
 step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst,
@@ -395,10 +430,11 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
     constexpr int LW = NT + 4;          // psi rings: lanes plus 2 columns each side
     constexpr int kWaves = NT / 64;
     constexpr int kHpw = 4 / kWaves;
-    constexpr int RS = Step2Smem<P, NT>::RS, RS2 = Step2Smem<P, NT>::RS2, NF = Step2Smem<P, NT>::NF;
-    C (&ring)[RS][LW] = sm.ring;
-    C (&ring2)[RS2][LW] = sm.ring2;
-    S (&fs)[NF][9][NT] = sm.fs;
+    constexpr int U = Step2Smem<P, NT>::U, NF = Step2Smem<P, NT>::NF;
+    C (&ring)[U][LW] = sm.ring;
+    C (&ring2)[U][LW] = sm.ring2;
+    S* const fs = &sm.fs[0][0][0];
+    constexpr int FR = 9 * NT;          // one row of fs
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -408,7 +444,7 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
     const int x0 = sx * W;              // first output column
     const int y0 = sy * g.tile_y;
     const int y1 = min(y0 + g.tile_y, g.ny);
-    const int dir = (sy & 1) ? -1 : 1;
+    const int dir = ((sy + (int)(k.step >> 1)) & 1) ? -1 : 1;
     const int ystart = dir > 0 ? y0 : y1 - 1;
     const int nrows = y1 - y0;
     const int nx = g.nx, ny = g.ny;
@@ -435,126 +471,130 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
     const int xc = modn(xb + tid, nx);
     const int xcm = xc == 0 ? nx - 1 : xc - 1;
     const int xcp = xc == nx - 1 ? 0 : xc + 1;
+    // A uniform row base plus a 32-bit lane offset needs no 64-bit vector add.
+    auto pull32 = [&](int rm, int r0, int rp, S (&f)[9]) {
+        constexpr uint32_t kB = sizeof(S);
+        const int rows[3] = {rp, r0, rm};
+        uint32_t cols[3] = {xcp * kB, xc * kB, xcm * kB};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) asm volatile("" : "+v"(cols[i]));
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            f[i] = *at32(pl[i] + rows[1 + kQCy[i]], cols[1 + kQCx[i]]);
+    };
+    auto decode = [&](const S (&v)[9], C (&f)[9]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = o.dec(v[i], o.of(i));
+    };
     // Level-2 output: lanes 3 .. 3+W-1, column x0 + tid - 3.
     const bool own2 = tid >= 3 && tid < 3 + W && x0 + tid - 3 < nx;
 
-    // Halo columns of level 1 (xb-2, xb-1, xb+NT, xb+NT+1), gathered as in
-    // the one-step walk.
-    const int hj = lane < 9 * kHpw ? lane : 9 * kHpw - 1;
-    const int hi = hj % 9;
-    const int hcol = wid * kHpw + hj / 9;
+    // Halo columns of level 1 (xb-2, xb-1, xb+NT, xb+NT+1): a column is held
+    // by 16 lanes, its populations in the lanes' order 1 3 2 4 5 7 6 8 0, so
+    // that the density's sum needs only shifts within the 16 lanes.
+    const int hj = lane & 15;
+    const int hi = hj < 8 ? (int)(0x86754231u >> (4 * hj)) & 15 : 0;
+    const int hcol = wid * kHpw + (lane >> 4) % kHpw;
     const int hlds = hcol < 2 ? hcol : NT + hcol;
     const int hgx = modn(xb - 2 + hlds - q_cx(hi), nx);
     const S* hp = src + (int64_t)hi * g.plane + hgx;
     const int hcy = q_cy(hi);
     const C hoff = o.of(hi);
-    const int mcol = wid * kHpw + (lane < kHpw ? lane : 0);
-    const int mlds = mcol < 2 ? mcol : NT + mcol;
-    const int gbase = 9 * (lane < kHpw ? lane : 0);
-    auto halo_load = [&](int y) -> C {
-        const int ym = y == 0 ? ny - 1 : y - 1;
-        const int yp = y == ny - 1 ? 0 : y + 1;
-        const int r = (hcy > 0 ? ym : (hcy < 0 ? yp : y)) * g.pitch;
-        return o.ld(hp + r, hoff);
+    const bool hown = hj == 0 && lane < 16 * kHpw;
+    // rm, r0, rp: offsets of rows y - 1, y, y + 1 in a plane.
+    auto halo_load = [&](int rm, int r0, int rp) -> S { return hp[hcy > 0 ? rm : (hcy < 0 ? rp : r0)]; };
+    auto halo_psi = [&](S raw, int slot) {
+        const C hv = o.dec(raw, hoff);
+        const C pair = hv + row_move<0xB1>(hv);             // 1 + 3, 2 + 4, 5 + 7, 6 + 8
+        const C diag = pair + row_move<0x102>(pair);        // lane 4: (5 + 7) + (6 + 8)
+        const C axis = (row_move<0x108>(hv) + pair) + row_move<0x102>(pair);
+        const C ps = psi_of(axis + row_move<0x104>(diag), k);
+        if (hown) ring[slot][hlds] = ps;
     };
-    auto halo_psi = [&](C hv, int slot) {
-        C h[9];
-#pragma unroll
-        for (int m = 0; m < 9; ++m) h[m] = __shfl(hv, gbase + m, 64);
-        const C ps = psi_of(density(h), k);
-        if (lane < kHpw) ring[slot][mlds] = ps;
+    auto load = [&](int y, S (&f)[9], S& hv) {
+        const int r0 = y * g.pitch;
+        const int rm = (y == 0 ? ny - 1 : y - 1) * g.pitch, rp = (y == ny - 1 ? 0 : y + 1) * g.pitch;
+        pull32(rm, r0, rp, f);
+        hv = halo_load(rm, r0, rp);
     };
 
-    // Level-1 walk row p lives in Bf[(p + 3) % NBF] (p >= -3); the level-2
-    // pre-collision row formed at iteration it in F2[(it + 2) % NBF].  The
-    // loads of a row are written LEAD iterations before its psi is staged:
-    // one for single precision; two for the half storage, whose loop then
-    // unrolls five-fold.  The compiler moves those loads back next to their
-    // use (the source is read-only), and for the five-fold loop it needs
-    // fewer registers (165 against 173: three waves per SIMD, not two).
-    constexpr int LEAD = P::kDev ? 2 : 1;
-    constexpr int NBF = 3 + LEAD;
-    C Bf[NBF][9] = {};
-    C Hh[NBF] = {};
-    C F2[NBF][9] = {};
+    // Level-1 walk row p lives in Bf[(p + 3) % U] (p >= -3); the level-2
+    // pre-collision row formed at iteration it in F2[(it + 2) % U].  The
+    // loads of a row are written LEAD iterations before its psi is staged.
+    // At tau = 1 the collision needs no more of a row than its moments, taken
+    // where its psi is staged: three registers a row wait for it, not nine.
+    constexpr int LEAD = kStep2Lead<P>;
+    constexpr bool kMom = kOm == 1;
+    S Raw[U][9] = {}, Hh[U] = {};
+    C Bf[U][9] = {}, F2[U][9] = {};
+    Moments<C> M1[U] = {}, M2[U] = {};
 
     // Prologue: psi at t of walk rows -5 .. -1 into ring slots 0 .. 4 and
     // the populations of rows -3 .. -1 into Bf[0 .. 2].
     {
-        C T0[9], T1[9], hv[5];
-        pull<P>(pl, g, xc, xcm, xcp, wrow(-5), o, T0);
-        pull<P>(pl, g, xc, xcm, xcp, wrow(-4), o, T1);
+        S T[5][9], hv[5];
 #pragma unroll
-        for (int r = 0; r < 3; ++r) pull<P>(pl, g, xc, xcm, xcp, wrow(r - 3), o, Bf[r]);
+        for (int r = 0; r < 5; ++r) load(wrow(r - 5), T[r], hv[r]);
 #pragma unroll
-        for (int r = 0; r < 5; ++r) hv[r] = halo_load(wrow(r - 5));
-        ring[0][tid + 2] = psi_of(density(T0), k);
-        ring[1][tid + 2] = psi_of(density(T1), k);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) ring[r + 2][tid + 2] = psi_of(density(Bf[r]), k);
+        for (int r = 0; r < 5; ++r) {
+            C f[9];
+            decode(T[r], f);
+            ring[r][tid + 2] = psi_of(density(f), k);
+            if (r >= 2) {
+                M1[r - 2] = moments(f);
+                for (int i = 0; i < 9; ++i) Bf[r - 2][i] = f[i];
+            }
+        }
 #pragma unroll
         for (int r = 0; r < 5; ++r) halo_psi(hv[r], r);
         // Rows 0 .. LEAD - 2: their loads stay in flight into the walk.
 #pragma unroll
-        for (int r = 0; r < LEAD - 1; ++r) {
-            pull<P>(pl, g, xc, xcm, xcp, wrow(r), o, Bf[3 + r]);
-            Hh[3 + r] = halo_load(wrow(r));
-        }
+        for (int r = 0; r < LEAD - 1; ++r) load(wrow(r), Raw[3 + r], Hh[3 + r]);
     }
     __syncthreads();
 
-    // One iteration per level-1 row p = it - 3, it = 0 .. nrows + 6.
-    auto group = [&](auto Jc, int it, int s0) {
-        constexpr int J = decltype(Jc)::value;  // it % NBF
+    int yl = wrow(LEAD - 2);  // lattice row of the last loaded walk row
+    // One iteration per level-1 row p = it - 3, it = 0 .. nrows + 6; it % U = J.
+    // All of it but the last collision runs at every row: where a row's
+    // neighbours are not there yet, or no longer needed, it forms values that
+    // nothing reads, and without branches the phases interleave.
+    auto group = [&](auto Jc, int it) {
+        constexpr int J = decltype(Jc)::value;
         const int p = it - 3;
         set_row_priority(it);
-        // ring2 holds walk row r in slot (r + 12) % RS2.  s0 = it % RS,
-        // so walk row p - 6 + k sits in slot b2 + k (mod RS2), k = 0 .. 4,
-        // with no division.
-        const int b2 = s0 >= 3 ? s0 - 3 : s0 + 3;
-        auto slot2 = [&](int kk) {
-            const int v = b2 + kk;
-            return v >= RS2 ? v - RS2 : v;
-        };
-        // Lead row p + 2 + LEAD (psi at t is needed up to row nrows + 4).
-        {
-            const int r = p + 2 + LEAD;
-            const int yl = r < nrows + 5 ? wrow(r) : wrow(p);
-            pull<P>(pl, g, xc, xcm, xcp, yl, o, Bf[(J + 2 + LEAD) % NBF]);
-            Hh[(J + 2 + LEAD) % NBF] = halo_load(yl);
-        }
+        // Lead row p + 2 + LEAD (psi at t is needed up to row nrows + 4; past
+        // it the last row again).
+        yl = p + 2 + LEAD < nrows + 5 ? wrapi(yl + dir, ny) : yl;
+        load(yl, Raw[(J + 2 + LEAD) % U], Hh[(J + 2 + LEAD) % U]);
+        __builtin_amdgcn_sched_barrier(0);
 
         // Level 2, part 1: pre-collision populations at t+1 of row p - 2
-        // (pulled from the ring rows p-3 .. p-1) and their psi.
-        if (p >= 0) {
-            // Formed here, collided two iterations later (which reads F2[J]).
-            C(&Fr)[9] = F2[(J + 2) % NBF];
+        // (pulled from the ring rows p-3 .. p-1) and their psi.  Formed here,
+        // collided two iterations later (which reads F2[J]).  Population i
+        // comes from row y - c_y, which is walk row p - 2 - c_y dir, lane
+        // l - c_x (lanes 0 and NT-1 form values no output uses).
+        {
+            C(&Fr)[9] = F2[(J + 2) % U];
+            const S* const row[3] = {fs + (dir > 0 ? J % NF : (J + 2) % NF) * FR + tid, fs + (J + 3) % NF * FR + tid,
+                                     fs + (dir > 0 ? (J + 2) % NF : J % NF) * FR + tid};
 #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                // f_i(x, t+1) = f*_i(x - c_i): lattice row y - c_y is walk
-                // row r - c_y dir; lane l - c_x (clamped: lanes 0 and NT-1
-                // form values no output uses).
-                const int rr = p - 2 - q_cy(i) * dir;
-                const int li = min(max(tid - q_cx(i), 0), NT - 1);
-                Fr[i] = o.ld(&fs[(rr + 4) & 3][i][li], o.of(i));
-            }
-            ring2[slot2(4)][tid + 2] = psi_of(density(Fr), k2);
+            for (int i = 0; i < 9; ++i) Fr[i] = o.dec(row[1 + kQCy[i]][i * NT - kQCx[i]], o.of(i));
+            M2[(J + 2) % U] = moments(Fr);
+            ring2[J % U][tid + 2] = psi_of(M2[(J + 2) % U].rho, k2);
         }
 
-        // Level 1: force and collision of row p into the ring of t+1.
-        C anchor = (C)0;
-        if (p <= nrows + 2) {
-            auto slot = [&](int dy) {
-                int v = s0 + 2 + dy * dir;
-                return v >= RS ? v - RS : v;
-            };
-            const Stencil<C> st(ring[slot(-2)], ring[slot(-1)], ring[slot(0)], ring[slot(1)],
-                                ring[slot(2)], tid + 2);
+        // Level 1: force and collision of row p into the ring of t+1.  The
+        // stencil's rows are taken in walk order.
+        C anchor;
+        {
+            const Stencil<C> st(ring[J % U], ring[(J + 1) % U], ring[(J + 2) % U], ring[(J + 3) % U],
+                                ring[(J + 4) % U], tid + 2);
             C q[9];
-            site_collide<false, P::kDev, kOm>(Bf[J % NBF], st, k, q, (C*)nullptr, o.o1, o.o2);
+            site_collide<false, P::kDev, kOm>(Bf[J % U], kMom ? M1[J % U] : moments(Bf[J % U]), st, k, q, (C*)nullptr,
+                                              o.o1, o.o2, dir < 0);
             S* lp[9];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) lp[i] = &fs[(p + 4) & 3][i][0];
+            for (int i = 0; i < 9; ++i) lp[i] = fs + (J + 1) % NF * FR + i * NT;
             const uint32_t rnd = P::kDev ? site_hash(xc, wrow(p), k.step) : 0u;
             store_site<P>(lp, tid, q, o, rnd);
             anchor = q[1];
@@ -562,15 +602,16 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
 
         // Stage psi at t of row p + 3.
         {
-            C(&NFr)[9] = Bf[(J + 3) % NBF];
-            C& HF = Hh[(J + 3) % NBF];
+            C(&NFr)[9] = Bf[(J + 3) % U];
+            S(&raw)[9] = Raw[(J + 3) % U];
+            S& HF = Hh[(J + 3) % U];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(NFr[i]) : "v"(anchor));
+            for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(raw[i]) : "v"(anchor));
             asm volatile("" : "+v"(HF) : "v"(anchor));
-            int sl = s0 + 5;
-            sl = sl >= RS ? sl - RS : sl;
-            ring[sl][tid + 2] = psi_of(density(NFr), k);
-            halo_psi(HF, sl);
+            decode(raw, NFr);
+            M1[(J + 3) % U] = moments(NFr);
+            ring[(J + 5) % U][tid + 2] = psi_of(M1[(J + 3) % U].rho, k);
+            halo_psi(HF, (J + 5) % U);
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
@@ -579,62 +620,61 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
         // psi rows q-2 .. q+2 at t+1; store.
         const int qr = p - 4;
         if (qr >= 0 && qr < nrows) {
-            // Walk rows are in walk order; psi row qr + dy (slot2(2 + dy)) is
-            // lattice row ystart + (qr + dy) dir, i.e. the stencil's y + dy dir.
-            const C* r_m2 = ring2[slot2(2 - 2 * dir)];
-            const C* r_m1 = ring2[slot2(2 - dir)];
-            const C* r_c = ring2[slot2(2)];
-            const C* r_p1 = ring2[slot2(2 + dir)];
-            const C* r_p2 = ring2[slot2(2 + 2 * dir)];
-            const Stencil<C> st2(r_m2, r_m1, r_c, r_p1, r_p2, tid + 2);
+            const Stencil<C> st2(ring2[(J + 4) % U], ring2[(J + 5) % U], ring2[(J + 6) % U], ring2[(J + 7) % U],
+                                 ring2[J % U], tid + 2);
             C q2[9];
-            site_collide<false, P::kDev, kOm>(F2[J % NBF], st2, k2, q2, (C*)nullptr, o.o1, o.o2);
+            site_collide<false, P::kDev, kOm>(F2[J % U], kMom ? M2[J % U] : moments(F2[J % U]), st2, k2, q2,
+                                              (C*)nullptr, o.o1, o.o2, dir < 0);
             if (own2) {
                 const int yq = wrow(qr);
                 const int xq = x0 + tid - 3;
+                uint32_t cq = (uint32_t)xq * (uint32_t)sizeof(S);
+                asm volatile("" : "+v"(cq));
                 const uint32_t rnd = P::kDev ? site_hash(xq, yq, k2.step) : 0u;
-                store_site<P>(pd, yq * g.pitch + xq, q2, o, rnd);
+                S* row[9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) row[i] = at32(pd[i] + yq * g.pitch, cq);
+                store_site<P>(row, 0, q2, o, rnd);
             }
         }
     };
 
-    auto step_slot = [](int s) { return s + 1 >= RS ? s + 1 - RS : s + 1; };
-    int s0 = 0;  // ring slot of level-1 walk row p - 2
     const int iters = nrows + 7;
 #pragma unroll 1
     for (int it = 0;;) {
-        group(Ic<0>{}, it, s0);
-        s0 = step_slot(s0);
+        group(Ic<0>{}, it);
         if (++it >= iters) break;
-        group(Ic<1>{}, it, s0);
-        s0 = step_slot(s0);
+        group(Ic<1>{}, it);
         if (++it >= iters) break;
-        group(Ic<2>{}, it, s0);
-        s0 = step_slot(s0);
+        group(Ic<2>{}, it);
         if (++it >= iters) break;
-        group(Ic<3>{}, it, s0);
-        s0 = step_slot(s0);
+        group(Ic<3>{}, it);
         if (++it >= iters) break;
-        if constexpr (NBF > 4) {
-            group(Ic<4>{}, it, s0);
-            s0 = step_slot(s0);
-            if (++it >= iters) break;
-        }
+        group(Ic<4>{}, it);
+        if (++it >= iters) break;
+        group(Ic<5>{}, it);
+        if (++it >= iters) break;
+        group(Ic<6>{}, it);
+        if (++it >= iters) break;
+        group(Ic<7>{}, it);
+        if (++it >= iters) break;
     }
 }
 
-template <class P, int NT>
-__global__ void __launch_bounds__(NT)
+// At least three waves per SIMD: without the bound the kernel for any tau
+// takes 188 registers and two.  Four (128 registers, 8 bytes spilled) are slower
+// at tau = 1: half storage 8192^2 387 us per step against 362.
+template <class P, int NT, int kOm>
+__global__ void __launch_bounds__(NT, 3)
 k_step2(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, Geom g,
         CoefT<typename P::C> k)
 {
-    // tau = 1 (every run of the paper) and other tau as separate walks, so
-    // the collision has no branch inside the loop.
+    // tau = 1 (every run of the paper) and other tau as separate kernels: the
+    // collision has no branch inside the loop, and the walk at tau = 1, which
+    // keeps three moments of a waiting row instead of its nine populations,
+    // is not given the registers of the other.
     __shared__ Step2Smem<P, NT> sm;
-    if (k.omega == (typename P::C)1)
-        step2_tile<P, NT, 1>(src, dst, g, k, xcd_remap(blockIdx.x, gridDim.x), sm);
-    else
-        step2_tile<P, NT, 0>(src, dst, g, k, xcd_remap(blockIdx.x, gridDim.x), sm);
+    step2_tile<P, NT, kOm>(src, dst, g, k, xcd_remap(blockIdx.x, gridDim.x), sm);
 }
 
 // One launch = one time step of one lattice: workgroup b updates logical
@@ -653,8 +693,8 @@ k_step(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst,
 // geometry, coefficients and buffers sit in desc.  Every lattice's tile is
 // processed exactly as the single-lattice kernel processes it, so fields
 // are bit-identical to single-lattice runs with the same tile shape.
-template <class P, int NT>
-__global__ void __launch_bounds__(NT)
+template <class P, int NT, bool kTau1>
+__global__ void __launch_bounds__(NT, 3)
 k_step2_batch(const BatchLattice* __restrict__ desc, const int32_t* __restrict__ tile_lattice,
               int parity, uint32_t step)
 {
@@ -666,8 +706,10 @@ k_step2_batch(const BatchLattice* __restrict__ desc, const int32_t* __restrict__
     const float* cf = d.coef_f;
     const CoefT<float> k{cf[0], cf[1], cf[2],  cf[3],  cf[4],  cf[5], cf[6],
                          cf[7], cf[8], cf[9], cf[10], cf[11], cf[12], step};
-    __shared__ Step2Smem<P, NT> sm;  // tau = 1 and other tau as separate walks
-    if (k.omega == 1.0f)
+    // kTau1 states that tau is 1 in every lattice; else the walks for tau = 1 and
+    // for other tau share the kernel and its registers.
+    __shared__ Step2Smem<P, NT> sm;
+    if (kTau1 || k.omega == 1.0f)
         step2_tile<P, NT, 1>(static_cast<const S*>(d.buf[parity]), static_cast<S*>(d.buf[parity ^ 1]),
                              d.geom2, k, gl - d.tile_begin2, sm);
     else
@@ -865,8 +907,12 @@ hipError_t step2_nt(const void* src, void* dst, const Geom& g, const Coef& c, hi
 {
     using S = typename P::S;
     const auto k = convert<typename P::C>(c);
-    hipLaunchKernelGGL((k_step2<P, NT>), dim3(g.blocks), dim3(NT), 0, s, static_cast<const S*>(src),
-                       static_cast<S*>(dst), g, k);
+    if (k.omega == 1)
+        hipLaunchKernelGGL((k_step2<P, NT, 1>), dim3(g.blocks), dim3(NT), 0, s, static_cast<const S*>(src),
+                           static_cast<S*>(dst), g, k);
+    else
+        hipLaunchKernelGGL((k_step2<P, NT, 0>), dim3(g.blocks), dim3(NT), 0, s, static_cast<const S*>(src),
+                           static_cast<S*>(dst), g, k);
     return hipGetLastError();
 }
 
@@ -948,34 +994,38 @@ hipError_t step2_p(const void* src, void* dst, const Geom& g, const Coef& c, hip
     }
 }
 
-template <class P>
+template <class P, bool kTau1>
 hipError_t step2_batch_p(int tile_x, const BatchLattice* desc, const int32_t* tile_lattice,
                          int tiles, int parity, uint32_t step, hipStream_t s)
 {
     const dim3 grid(tiles);
     switch (tile_x) {
     case 64:
-        hipLaunchKernelGGL((k_step2_batch<P, 64>), grid, dim3(64), 0, s, desc, tile_lattice, parity, step);
+        hipLaunchKernelGGL((k_step2_batch<P, 64, kTau1>), grid, dim3(64), 0, s, desc, tile_lattice, parity, step);
         break;
     case 128:
-        hipLaunchKernelGGL((k_step2_batch<P, 128>), grid, dim3(128), 0, s, desc, tile_lattice, parity, step);
+        hipLaunchKernelGGL((k_step2_batch<P, 128, kTau1>), grid, dim3(128), 0, s, desc, tile_lattice, parity, step);
         break;
     case 256:
-        hipLaunchKernelGGL((k_step2_batch<P, 256>), grid, dim3(256), 0, s, desc, tile_lattice, parity, step);
+        hipLaunchKernelGGL((k_step2_batch<P, 256, kTau1>), grid, dim3(256), 0, s, desc, tile_lattice, parity, step);
         break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_step2_batch(int storage, int tile_x, const BatchLattice* desc,
+hipError_t launch_step2_batch(int storage, bool tau1, int tile_x, const BatchLattice* desc,
                               const int32_t* tile_lattice, int tiles, int parity, uint32_t step,
                               hipStream_t s)
 {
     if (tiles <= 0) return hipErrorInvalidValue;
     switch (storage) {
-    case ST_F32: return step2_batch_p<PF32>(tile_x, desc, tile_lattice, tiles, parity, step, s);
-    case ST_F16DEV: return step2_batch_p<PF16>(tile_x, desc, tile_lattice, tiles, parity, step, s);
+    case ST_F32:
+        return tau1 ? step2_batch_p<PF32, true>(tile_x, desc, tile_lattice, tiles, parity, step, s)
+                    : step2_batch_p<PF32, false>(tile_x, desc, tile_lattice, tiles, parity, step, s);
+    case ST_F16DEV:
+        return tau1 ? step2_batch_p<PF16, true>(tile_x, desc, tile_lattice, tiles, parity, step, s)
+                    : step2_batch_p<PF16, false>(tile_x, desc, tile_lattice, tiles, parity, step, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -995,9 +1045,9 @@ template <class P>
 const void* step2_kernel(int tile_x)
 {
     switch (tile_x) {
-    case 64: return reinterpret_cast<const void*>(k_step2<P, 64>);
-    case 128: return reinterpret_cast<const void*>(k_step2<P, 128>);
-    case 256: return reinterpret_cast<const void*>(k_step2<P, 256>);
+    case 64: return reinterpret_cast<const void*>(k_step2<P, 64, 0>);
+    case 128: return reinterpret_cast<const void*>(k_step2<P, 128, 0>);
+    case 256: return reinterpret_cast<const void*>(k_step2<P, 256, 0>);
     default: return nullptr;
     }
 }

@@ -207,6 +207,19 @@ __device__ __forceinline__ void store_site(typename P::S* const* pd, int at,
     }
 }
 
+// The element `bytes` after base: a uniform base plus a 32-bit lane offset needs
+// no 64-bit vector arithmetic per access.
+template <typename T>
+__device__ __forceinline__ const T* at32(const T* base, uint32_t bytes)
+{
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+template <typename T>
+__device__ __forceinline__ T* at32(T* base, uint32_t bytes)
+{
+    return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
+}
+
 // Pull the nine populations arriving at (x, y): f_i(x, t) = stored_i(x - c_i).
 // xm/xp are the periodic columns x-1 / x+1.
 template <class P>
@@ -284,18 +297,35 @@ struct Stencil {
     }
 };
 
+// Density and momentum of one site's populations.
+template <typename C>
+struct Moments {
+    C rho, jx, jy;
+};
+template <typename C>
+__device__ __forceinline__ Moments<C> moments(const C (&R)[9])
+{
+#pragma clang fp contract(off)
+    return {density(R), (R[1] - R[3]) + ((R[5] - R[7]) + (R[8] - R[6])),
+            (R[2] - R[4]) + ((R[5] - R[7]) + (R[6] - R[8]))};
+}
+
 // Force of eq. (FORCE) and the velocity-shift BGK collision at one site: R
-// the pre-collision populations, st the psi stencil around the site, Q the
+// the pre-collision populations (unread at kOm = 1), m their moments, st the
+// psi stencil around the site, Q the
 // post-collision populations; with kTape also the tape entry.  For the half
 // storage (kDev) Q[0] is the density and Q[1..8] the deviations
 // f*_i - w_i rho_ref from the offsets o1 (axis) and o2 (diagonal), which at
 // tau = 1 come out of one fma each.  kOm = 1 or 0 states that tau is 1, or
 // is not, for a caller that has branched on it already; -1 tests k.omega.
+// With mirror the stencil's rows come in the order y+2 .. y-2: every sum of
+// the force is then the same value (x) or its exact negative (y).
 // Every kernel that updates a site calls this, so all of them round
 // identically.
 template <bool kTape, bool kDev, int kOm = -1, typename C>
-__device__ __forceinline__ void site_collide(const C (&R)[9], const Stencil<C>& st, const CoefT<C>& k,
-                                             C (&Q)[9], C* tp, C o1 = (C)0, C o2 = (C)0)
+__device__ __forceinline__ void site_collide(const C (&R)[9], const Moments<C>& m, const Stencil<C>& st,
+                                             const CoefT<C>& k, C (&Q)[9], C* tp, C o1 = (C)0, C o2 = (C)0,
+                                             bool mirror = false)
 {
 #pragma clang fp contract(off)
     // Multiply-adds are written out as fma and nothing else is contracted,
@@ -321,12 +351,10 @@ __device__ __forceinline__ void site_collide(const C (&R)[9], const Stencil<C>& 
                     fma_c(k.K4x2, st.n2 - st.s2v,
                           fma_c(k.K5, fma_c((C)2, d5c + d5d, d5a - d5b), k.K8x2 * (d8a - d8b)))));
     const C Fx = -p * sumx;
-    const C Fy = -p * sumy;
+    const C Fy = (mirror ? p : -p) * sumy;
 
     // BGK collision at u_eq = (j + tau F) / rho.
-    const C rho = density(R);
-    const C jx = (R[1] - R[3]) + ((R[5] - R[7]) + (R[8] - R[6]));
-    const C jy = (R[2] - R[4]) + ((R[5] - R[7]) + (R[6] - R[8]));
+    const C rho = m.rho, jx = m.jx, jy = m.jy;
     if (kTape) {
         tp[0] = rho;
         tp[1] = jx;

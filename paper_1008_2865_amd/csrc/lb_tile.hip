@@ -29,14 +29,6 @@
 namespace lbk {
 namespace {
 
-// base[e] for an element offset whose byte offset fits 32 bits: a uniform base
-// plus a 32-bit lane offset needs no 64-bit address arithmetic per load.
-template <typename T>
-__device__ __forceinline__ const T* at32(const T* base, int e)
-{
-    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)e * (uint32_t)sizeof(T));
-}
-
 // Tile lb of a lattice.
 template <class P, int NT, int kPitch, int kRows, bool kTape>
 __device__ __forceinline__ void
@@ -94,7 +86,7 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
                 const int ys[3] = {gy == ny - 1 ? 0 : r + g.pitch, r, gy == 0 ? (ny - 1) * g.pitch : r - g.pitch};
 #pragma unroll
                 for (int q = 0; q < 9; ++q)
-                    F[i][q] = o.ld(at32(pl[q], ys[1 + kQCy[q]] + xs[1 + kQCx[q]]), o.of(q));
+                    F[i][q] = o.ld(at32(pl[q], (uint32_t)(ys[1 + kQCy[q]] + xs[1 + kQCx[q]]) * (uint32_t)sizeof(S)), o.of(q));
             }
         } else {
 #pragma unroll
@@ -126,7 +118,7 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             const int c = (y + in) * kPitch + x + in;
             const Stencil<C> st(psi - 2 * kPitch, psi - kPitch, psi, psi + kPitch, psi + 2 * kPitch, c);
             C q[9], tp[4];
-            site_collide<kTape, P::kDev>(F[i], st, k, q, tp, o.o1, o.o2);
+            site_collide<kTape, P::kDev>(F[i], moments(F[i]), st, k, q, tp, o.o1, o.o2);
             const int ux = x0 - halo + x, uy = y0 - halo + y;  // before the periodic wrap
             const bool own = ux >= x0 && ux < min(x0 + g.tx, nx) && uy >= y0 && uy < min(y0 + g.ty, ny);
             const uint32_t rnd = P::kDev ? site_hash(wrapi(ux, nx), wrapi(uy, ny), k.step + j) : 0u;
