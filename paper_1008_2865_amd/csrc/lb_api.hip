@@ -1389,12 +1389,13 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     b->tile.tx = L.tile.tx;
     b->tile.ty = L.tile.ty;
     b->tile.threads = L.tile.threads;
+    b->tile.tau1 = std::all_of(ps, ps + count, [](const lb_params& p) { return 1.0 / p.tau == 1.0; });
     b->tile_steps = L.tile.steps;
     b->partials = reinterpret_cast<double*>(ws + L.partials);
     b->tiles = L.tiles;
     b->tiles2 = L.tiles2;
     b->two = L.two;
-    b->tau1 = std::all_of(ps, ps + count, [](const lb_params& p) { return 1.0 / p.tau == 1.0; });
+    b->tau1 = b->tile.tau1;
     b->tile_x2 = 128;
     b->tile_y2 = L.tile_y2;
     b->storage = ps[0].storage;

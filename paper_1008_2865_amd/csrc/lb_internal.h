@@ -134,6 +134,7 @@ struct TileBatch {
     int tiles, tx, ty, threads;
     int parity, steps;            // reads buf[parity], writes buf[parity ^ 1]
     uint32_t step;                // time level of the first step
+    bool tau1;                    // tau is 1 in every lattice
 };
 hipError_t launch_tile_batch(int storage, const TileBatch& b, hipStream_t s);
 hipError_t launch_final(const double* partials, int blocks, double t,

@@ -244,7 +244,7 @@ step_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst
             }
 
             if (kCollide) {
-                site_collide<kTape, P::kDev>(R, moments(R), st, k, q[m], tp[m], o.o1, o.o2);
+                site_collide<kTape, P::kDev>(R, (const Moments<C>*)nullptr, st, k, q[m], tp[m], o.o1, o.o2);
                 if (m == 0) anchor = q[m][1];
             } else if (m == 0) {
                 anchor = p;
@@ -590,7 +590,7 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             const Stencil<C> st(ring[J % U], ring[(J + 1) % U], ring[(J + 2) % U], ring[(J + 3) % U],
                                 ring[(J + 4) % U], tid + 2);
             C q[9];
-            site_collide<false, P::kDev, kOm>(Bf[J % U], kMom ? M1[J % U] : moments(Bf[J % U]), st, k, q, (C*)nullptr,
+            site_collide<false, P::kDev, kOm>(Bf[J % U], kMom ? &M1[J % U] : nullptr, st, k, q, (C*)nullptr,
                                               o.o1, o.o2, dir < 0);
             S* lp[9];
 #pragma unroll
@@ -623,7 +623,7 @@ step2_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             const Stencil<C> st2(ring2[(J + 4) % U], ring2[(J + 5) % U], ring2[(J + 6) % U], ring2[(J + 7) % U],
                                  ring2[J % U], tid + 2);
             C q2[9];
-            site_collide<false, P::kDev, kOm>(F2[J % U], kMom ? M2[J % U] : moments(F2[J % U]), st2, k2, q2,
+            site_collide<false, P::kDev, kOm>(F2[J % U], kMom ? &M2[J % U] : nullptr, st2, k2, q2,
                                               (C*)nullptr, o.o1, o.o2, dir < 0);
             if (own2) {
                 const int yq = wrow(qr);

@@ -311,8 +311,9 @@ __device__ __forceinline__ Moments<C> moments(const C (&R)[9])
 }
 
 // Force of eq. (FORCE) and the velocity-shift BGK collision at one site: R
-// the pre-collision populations (unread at kOm = 1), m their moments, st the
-// psi stencil around the site, Q the
+// the pre-collision populations, m their moments if the caller has them (R is
+// then unread at kOm = 1; taken here, after the force, they occupy registers for
+// less long), st the psi stencil around the site, Q the
 // post-collision populations; with kTape also the tape entry.  For the half
 // storage (kDev) Q[0] is the density and Q[1..8] the deviations
 // f*_i - w_i rho_ref from the offsets o1 (axis) and o2 (diagonal), which at
@@ -323,7 +324,7 @@ __device__ __forceinline__ Moments<C> moments(const C (&R)[9])
 // Every kernel that updates a site calls this, so all of them round
 // identically.
 template <bool kTape, bool kDev, int kOm = -1, typename C>
-__device__ __forceinline__ void site_collide(const C (&R)[9], const Moments<C>& m, const Stencil<C>& st,
+__device__ __forceinline__ void site_collide(const C (&R)[9], const Moments<C>* m, const Stencil<C>& st,
                                              const CoefT<C>& k, C (&Q)[9], C* tp, C o1 = (C)0, C o2 = (C)0,
                                              bool mirror = false)
 {
@@ -354,7 +355,8 @@ __device__ __forceinline__ void site_collide(const C (&R)[9], const Moments<C>& 
     const C Fy = (mirror ? p : -p) * sumy;
 
     // BGK collision at u_eq = (j + tau F) / rho.
-    const C rho = m.rho, jx = m.jx, jy = m.jy;
+    const Moments<C> mo = m ? *m : moments(R);
+    const C rho = mo.rho, jx = mo.jx, jy = mo.jy;
     if (kTape) {
         tp[0] = rho;
         tp[1] = jx;

@@ -20,8 +20,8 @@
 // instructions per site and step, 1.2 to 1.4 times the sites for the halo.  A
 // row walk of one step per launch spends 4.6 to 7 us on any small lattice.
 // us/step before and after: FP32 64^2 4.4 -> 2.0, 256^2 5.6 -> 2.5, 512^2
-// 7.5 -> 4.5, 997x701 12.8 -> 9.4; FP64 64^2 6.4 -> 2.7, 512^2 13.5 -> 7.2,
-// 1200^2 44 -> 33, 2048^2 128 -> 98.
+// 7.5 -> 4.4, 997x701 12.8 -> 9.2; FP64 64^2 6.4 -> 2.7, 512^2 13.5 -> 7.0,
+// 1200^2 44 -> 33, 2048^2 128 -> 95.
 #include "lb_site.h"
 
 #include <type_traits>
@@ -29,8 +29,9 @@
 namespace lbk {
 namespace {
 
-// Tile lb of a lattice.
-template <class P, int NT, int kPitch, int kRows, bool kTape>
+// Tile lb of a lattice.  kOm as in site_collide; at 1 a site waits for its
+// collision as its three moments instead of its nine populations.
+template <class P, int NT, int kPitch, int kRows, bool kTape, int kOm>
 __device__ __forceinline__ void
 tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, const TileGeom& g, const int steps,
            const CoefT<typename P::C>& k, typename P::C* __restrict__ tape, const int lb)
@@ -74,6 +75,7 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             x = s - y * w;
         };
         C F[R][9];
+        Moments<C> M[R];
         if (j == 0) {
 #pragma unroll
             for (int i = 0; i < R; ++i) {
@@ -104,7 +106,8 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             if (i * NT >= ns) break;
             int x, y;
             site(i, x, y);
-            psi[(y + in) * kPitch + x + in] = psi_of(density(F[i]), k);
+            if (kOm == 1) M[i] = moments(F[i]);
+            psi[(y + in) * kPitch + x + in] = psi_of(kOm == 1 ? M[i].rho : density(F[i]), k);
         }
         __syncthreads();
 
@@ -118,7 +121,7 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
             const int c = (y + in) * kPitch + x + in;
             const Stencil<C> st(psi - 2 * kPitch, psi - kPitch, psi, psi + kPitch, psi + 2 * kPitch, c);
             C q[9], tp[4];
-            site_collide<kTape, P::kDev>(F[i], moments(F[i]), st, k, q, tp, o.o1, o.o2);
+            site_collide<kTape, P::kDev, kOm>(F[i], kOm == 1 ? &M[i] : nullptr, st, k, q, tp, o.o1, o.o2);
             const int ux = x0 - halo + x, uy = y0 - halo + y;  // before the periodic wrap
             const bool own = ux >= x0 && ux < min(x0 + g.tx, nx) && uy >= y0 && uy < min(y0 + g.ty, ny);
             const uint32_t rnd = P::kDev ? site_hash(wrapi(ux, nx), wrapi(uy, ny), k.step + j) : 0u;
@@ -136,18 +139,20 @@ tile_steps(const typename P::S* __restrict__ src, typename P::S* __restrict__ ds
     }
 }
 
-template <class P, int NT, int kPitch, int kRows, bool kTape>
-__global__ void __launch_bounds__(NT)
+// Two waves per SIMD in 256 threads: two workgroups fit a CU's LDS.  With one,
+// FP64 1200^2 takes 51 us/step instead of 34.
+template <class P, int NT, int kPitch, int kRows, bool kTape, int kOm>
+__global__ void __launch_bounds__(NT, NT == 256 ? 2 : 1)
 k_tile(const typename P::S* __restrict__ src, typename P::S* __restrict__ dst, TileGeom g,
        CoefT<typename P::C> k, typename P::C* __restrict__ tape)
 {
-    tile_steps<P, NT, kPitch, kRows, kTape>(src, dst, g, g.steps, k, tape, xcd_remap(blockIdx.x, gridDim.x));
+    tile_steps<P, NT, kPitch, kRows, kTape, kOm>(src, dst, g, g.steps, k, tape, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // The same for every lattice of a batch: the tiles of all lattices are
 // numbered consecutively, tile_lattice gives a tile's lattice.
-template <class P, int NT, int kPitch, int kRows>
-__global__ void __launch_bounds__(NT)
+template <class P, int NT, int kPitch, int kRows, int kOm>
+__global__ void __launch_bounds__(NT, NT == 256 ? 2 : 1)
 k_tile_batch(const BatchLattice* __restrict__ desc, const int32_t* __restrict__ tile_lattice, int parity,
              uint32_t step, int steps)
 {
@@ -162,7 +167,7 @@ k_tile_batch(const BatchLattice* __restrict__ desc, const int32_t* __restrict__ 
         k = convert<double>(d.coef);
         k.step = step;
     }
-    tile_steps<P, NT, kPitch, kRows, false>(static_cast<const S*>(d.buf[parity]),
+    tile_steps<P, NT, kPitch, kRows, false, kOm>(static_cast<const S*>(d.buf[parity]),
                                             static_cast<S*>(d.buf[parity ^ 1]), d.tile, steps, k, nullptr,
                                             gl - d.tile_begin3);
 }
@@ -176,7 +181,14 @@ size_t tile_lds(int steps)
     return psi + (steps > 1 ? post : 0);
 }
 
-template <class P, int NT, int kPitch, int kRows>
+// Whether tau = 1 has a kernel of its own.  us/step with one and without: FP32
+// 512^2 4.50 and 4.62, 997x701 9.27 and 9.53, half storage 512^2 4.35 and 4.42,
+// FP64 in 256 threads 1200^2 33.3 and 34.7, 2048^2 95.0 and 97.8; in 1024 threads,
+// which have no register to spare for the moments, FP64 64^2 3.02 and 2.92.
+template <typename C, int NT>
+constexpr bool kTau1Kernel = sizeof(C) == 4 || NT < 1024;
+
+template <class P, int NT, int kPitch, int kRows, int kOm>
 hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
 {
     using S = typename P::S;
@@ -189,10 +201,10 @@ hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c,
         if constexpr (P::kDev)
             return hipErrorInvalidValue;
         else
-            hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, true>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
+            hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, true, kOm>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
                                static_cast<C*>(tape));
     } else {
-        hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, false>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
+        hipLaunchKernelGGL((k_tile<P, NT, kPitch, kRows, false, kOm>), dim3(g.tiles), dim3(NT), lds, s, a, b, g, k,
                            static_cast<C*>(nullptr));
     }
     return hipGetLastError();
@@ -201,8 +213,11 @@ hipError_t tile_nt(const void* src, void* dst, const TileGeom& g, const Coef& c,
 template <class P, int NT, int kPitch, int kRows>
 hipError_t batch_nt(const TileBatch& b, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_tile_batch<P, NT, kPitch, kRows>), dim3(b.tiles), dim3(NT),
-                       (tile_lds<P, kPitch, kRows>(b.steps)), s, b.desc, b.tile_lattice, b.parity, b.step, b.steps);
+    // tau1: tau is 1 in every lattice; else each tile's collision tests its own.
+    constexpr int kOm = kTau1Kernel<typename P::C, NT> ? 1 : -1;
+    const auto kernel = b.tau1 ? k_tile_batch<P, NT, kPitch, kRows, kOm> : k_tile_batch<P, NT, kPitch, kRows, -1>;
+    hipLaunchKernelGGL(kernel, dim3(b.tiles), dim3(NT), (tile_lds<P, kPitch, kRows>(b.steps)), s, b.desc,
+                       b.tile_lattice, b.parity, b.step, b.steps);
     return hipGetLastError();
 }
 
@@ -238,7 +253,12 @@ template <class P>
 hipError_t tile_p(const void* src, void* dst, const TileGeom& g, const Coef& c, void* tape, hipStream_t s)
 {
     return with_shape<P>(g.threads, g.tx, g.ty, g.steps, [&](auto nt, auto region) {
-        return tile_nt<P, nt.value, region.w, region.h>(src, dst, g, c, tape, s);
+        using C = typename P::C;
+        if constexpr (!kTau1Kernel<C, nt.value>)
+            return tile_nt<P, nt.value, region.w, region.h, -1>(src, dst, g, c, tape, s);
+        else
+            return (C)c.omega == 1 ? tile_nt<P, nt.value, region.w, region.h, 1>(src, dst, g, c, tape, s)
+                                   : tile_nt<P, nt.value, region.w, region.h, 0>(src, dst, g, c, tape, s);
     });
 }
 

@@ -57,3 +57,25 @@ def test_lattices_hold_the_bits_of_their_own_runs(group, storage, use_graphs):
             assert ta.shape == tb.shape and np.array_equal(ta, tb), k
             single.close()
         batch.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+@pytest.mark.parametrize("tau", [1.0, 1.3])
+@pytest.mark.parametrize("group", ["small", "large"])
+def test_one_tau_for_every_lattice(group, tau, storage):
+    # A batch whose lattices all have tau = 1 runs a kernel of its own.
+    print(f"batch tile {storage} {group} tau {tau}", flush=True)
+    lats = []
+    for k, (nx, ny) in enumerate(SIZES[group]):
+        G1, G2 = inputs.couplings(0.03 * k)
+        lats.append(dict(rho_init=inputs.rho_noise(nx, ny, 80 + k), G1=G1, G2=G2, tau=tau))
+    with torch.cuda.stream(torch.cuda.Stream()):
+        batch = LBBatch(lats, storage=storage, tile_x=64)
+        batch.step(9)
+        for k, L in enumerate(lats):
+            single = LBSim(L["rho_init"], G1=L["G1"], G2=L["G2"], tau=tau, storage=storage, tile_x=64,
+                           steps_per_launch=1)
+            single.step(9)
+            assert np.array_equal(batch[k].get_state().view(np.uint8), single.get_state().view(np.uint8)), k
+            single.close()
+        batch.close()
