@@ -28,7 +28,7 @@ PEAK_HBM_GBPS = 8000.0
 BYTES_PER_LU = {"f64": 144, "f32": 72, "f16dev": 36}
 METRIC = "MLUPS and achieved HBM GB/s (two-belt D2Q9 step); adjoint/forward time ratio"
 TRAFFIC_FILES = sorted(glob.glob(os.path.join(ROOT, "profiles", "*_traffic.txt")))
-KERNEL_SRC = os.path.join(ROOT, "paper_1008_2865_amd", "csrc", "lb_kernels.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_1008_2865_amd", "csrc", f) for f in ("lb_kernels.hip", "lb_site.h")]
 
 
 def log(*a):
@@ -36,8 +36,11 @@ def log(*a):
 
 
 def kernel_source_hash():
-    with open(KERNEL_SRC, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SRC:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload_key):
@@ -351,7 +354,9 @@ def main():
     traffic = measured_traffic(workload_key)
     copy_gbps = copy_bandwidth(bpl // 2 * sites)
     kernel = ("k_step2 (two fused pull-stream + two-belt force + BGK collide steps per launch)"
-              if two else "k_step (fused pull-stream + two-belt force + BGK collide)")
+              if two else "k_tile (several steps per launch on LDS tiles; the figures are per step)"
+              if not (args.steps_per_launch or args.tile_x or args.tile_y or args.tile_rows)
+              else "k_step (fused pull-stream + two-belt force + BGK collide)")
     out = {
         "metric": METRIC,
         "value": round(value, 1),
@@ -589,10 +594,10 @@ def bench_adjoint(args):
 
 
 def bench_structure(args):
-    """The structure factor of section IV (mean, row FFTs, transpose, column
-    FFTs with |.|^2 / N, shell averages, kbar) on seeded density fields of
+    """The structure factor of section IV (mean, row FFTs of row pairs, column
+    FFTs with |.|^2 / N and the shells' sums, kbar) on seeded density fields of
     512^2 and 2048^2, FP64; GPU time per evaluation from HIP events on the
-    library's stream, synchronous host copies of the shells included."""
+    library's stream, the wait for the shells in host memory included."""
     import numpy as np
     import torch
 
@@ -620,11 +625,10 @@ def bench_structure(args):
         torch.cuda.synchronize()
         wall = (time.perf_counter() - t0) / reps
         gpu = a.elapsed_time(b) / 1e3 / reps
-        # Bytes of the two-pass transform: rho in, row spectra out (8 + 16),
-        # transpose (16 + 16), column spectra in, |.|^2 out (16 + 8), shell
-        # pass (8 + 4 index bytes) per mode.
+        # Bytes of the two passes per mode: rho in, half of the row spectra
+        # out and in again (8 + 8 + 8).
         res[L] = {"us_per_eval": round(gpu * 1e6, 2), "wall_us_per_eval": round(wall * 1e6, 2),
-                  "effective_gbps": round(92 * L * L / gpu / 1e9, 1), "kbar": kbar}
+                  "effective_gbps": round(24 * L * L / gpu / 1e9, 1), "kbar": kbar}
         log(f"bench: S(k) L={L}: {gpu * 1e6:.1f} us (GPU), {wall * 1e6:.1f} us (wall)")
         sk.close()
     out = {

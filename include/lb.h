@@ -198,9 +198,9 @@ const char* lb_last_error(void);
  * Batches: many independent periodic lattices, each with its own size,
  * couplings and initial density, advanced together by one kernel launch
  * per time step, or per several plain steps under the same rule as
- * lb_params.steps_per_launch, whatever the launch shape (the step of every lattice is exactly the one
- * lb_step performs, so its fields are bit-identical to a lb_step run of the
- * same lattice).
+ * lb_params.steps_per_launch, whatever the launch shape (the step of every
+ * lattice is exactly the one lb_step performs, so its fields are
+ * bit-identical to a lb_step run of the same lattice).
  * ------------------------------------------------------------------------ */
 typedef struct lb_batch lb_batch;
 
