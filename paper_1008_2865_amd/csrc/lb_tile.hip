@@ -184,7 +184,7 @@ size_t tile_lds(int steps)
 // Whether tau = 1 has a kernel of its own.  us/step with one and without: FP32
 // 512^2 4.50 and 4.62, 997x701 9.27 and 9.53, half storage 512^2 4.35 and 4.42,
 // FP64 in 256 threads 1200^2 33.3 and 34.7, 2048^2 95.0 and 97.8; in 1024 threads,
-// which have no register to spare for the moments, FP64 64^2 3.02 and 2.92.
+// which have no register to spare for the moments, FP64 64^2 3.05 and 2.78.
 template <typename C, int NT>
 constexpr bool kTau1Kernel = sizeof(C) == 4 || NT < 1024;
 
