@@ -2156,7 +2156,7 @@ int sk_check_L(int32_t L)
 
 struct SkLayout {
     lbk::SkFft fft;
-    size_t tw, chirp, filter, z, spec, part, count, rho, total;
+    size_t tw, chirp, filter, z, mean, spec, part, count, rho, total;
     int32_t nshell, hc, hp;
 };
 
@@ -2174,6 +2174,7 @@ SkLayout sk_layout(int32_t L)
     S.chirp = off; off += align_up((size_t)L * 2 * sizeof(double));
     S.filter = off; off += align_up((size_t)S.fft.m * 2 * sizeof(double));
     S.z = off; off += align_up((size_t)L * S.hc * 2 * sizeof(double));
+    S.mean = off; off += align_up((size_t)L * sizeof(double));
     S.spec = off; off += align_up((size_t)S.hp * L * sizeof(double));
     S.part = off; off += align_up((size_t)S.nshell * S.hp * sizeof(double));
     S.count = off; off += align_up((size_t)S.nshell * sizeof(double));
@@ -2253,6 +2254,7 @@ int lb_sk_init(lb_sk** out, int32_t L, void* workspace, size_t bytes, void* hip_
     double2* filter = reinterpret_cast<double2*>(ws + S.filter);
     p.t = lbk::SkTables{tw, chirp, filter};
     p.z = reinterpret_cast<double2*>(ws + S.z);
+    p.mean = reinterpret_cast<double*>(ws + S.mean);
     p.spec = reinterpret_cast<double*>(ws + S.spec);
     p.part = reinterpret_cast<double*>(ws + S.part);
     p.count = reinterpret_cast<const double*>(ws + S.count);

@@ -241,6 +241,7 @@ struct SkPlan {
     int32_t hp;          // L/2 + 1, columns of the half spectrum
     SkTables t;
     double2* z;          // L*hc: row spectra, [y][l]
+    double* mean;        // L: the numbers subtracted from the rows
     double* spec;        // hp*L: S at (l, m), l <= L/2, stored [l][m]
     double* part;        // nshell*hp: run sums, [n][l]
     const double* count; // nshell: modes per shell

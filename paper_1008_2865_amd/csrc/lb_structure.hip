@@ -334,13 +334,18 @@ __device__ __forceinline__ double pairwise(const double (&v)[kPerThread])
 }
 
 // Rows 2b and 2b + 1 of rho as the real and imaginary part of one line, each
-// less its own mean (which only l = 0 carries: that entry is the row's sum,
-// formed before the subtraction).  z[y][l], l < hc: the row spectra for
-// l = 0 .. hc - 1; for even L the real values at l = 0 and l = L/2 share
-// entry 0, as its real and imaginary part.  LDS: pad(f.m) + 2 elements.
+// less a number close to its mean, which mean[y] keeps: l = 0 of the transform is
+// then the sum of what is left, and neither it nor mean[y] - mean[0] carries the
+// rounding of the mean (S(0, m) of noise 1e-6 about 0.7 would be wrong by 5e-9 of
+// itself if the rows' plain sums were stored).  That number is taken from the
+// differences to the row's first value, so a uniform row leaves exact zeros.
+// z[y][l], l < hc: the row spectra for l = 0 .. hc - 1; for even L the real
+// values at l = 0 and l = L/2 share entry 0, as its real and imaginary part.
+// LDS: pad(f.m) + 2 elements.
 template <bool kChirp>
 __global__ void __launch_bounds__(kChirp ? 512 : 256)
-k_sk_rows(const double* __restrict__ rho, SkFft f, SkTables t, int hc, double2* __restrict__ z)
+k_sk_rows(const double* __restrict__ rho, SkFft f, SkTables t, int hc, double2* __restrict__ z,
+          double* __restrict__ mean)
 {
     extern __shared__ double2 lds[];
     __shared__ double red[2 * 16];
@@ -350,20 +355,27 @@ k_sk_rows(const double* __restrict__ rho, SkFft f, SkTables t, int hc, double2* 
     const bool two = ya + 1 < n;
     const double* ra = rho + ya * n;
     const double* rb = two ? ra + n : ra;
-    double va[kPerThread], vb[kPerThread];
+    const double a0 = ra[0], b0 = rb[0];
+    double va[kPerThread], vb[kPerThread], da[kPerThread], db[kPerThread];
 #pragma unroll
     for (int b = 0; b < kPerThread; ++b) {
         const int i = tid + b * T;
-        va[b] = i < n ? ra[i] : 0.0;
-        vb[b] = i < n ? rb[i] : 0.0;
+        va[b] = i < n ? ra[i] : a0;
+        vb[b] = i < n ? rb[i] : b0;
+        da[b] = va[b] - a0;
+        db[b] = vb[b] - b0;
     }
-    double sum[2] = {pairwise(va), pairwise(vb)};
+    double sum[2] = {pairwise(da), pairwise(db)};
     block_sum<2>(sum, red);
-    const double ma = sum[0] / (double)n, mb = sum[1] / (double)n;
+    const double ma = a0 + sum[0] / (double)n, mb = b0 + sum[1] / (double)n;
 #pragma unroll
     for (int b = 0; b < kPerThread; ++b) {
         const int i = tid + b * T;
         if (i < n) x[pad(i)] = make_double2(va[b] - ma, vb[b] - mb);
+    }
+    if (tid == 0) {
+        mean[ya] = ma;
+        if (two) mean[ya + 1] = mb;
     }
     __syncthreads();
     fft_lines<kChirp>(x, 1, 0, f, t);
@@ -375,8 +387,8 @@ k_sk_rows(const double* __restrict__ rho, SkFft f, SkTables t, int hc, double2* 
         double2 b = make_double2(0.5 * (p.y + q.y), 0.5 * (q.x - p.x));
         if (k == 0) {
             const double2 h = (n & 1) ? make_double2(0.0, 0.0) : x[pad(n / 2)];
-            a = make_double2(sum[0], h.x);
-            b = make_double2(sum[1], h.y);
+            a = make_double2(p.x, h.x);
+            b = make_double2(p.y, h.y);
         }
         za[k] = a;
         if (two) zb[k] = b;
@@ -406,14 +418,16 @@ __device__ __forceinline__ int shell_at(int l, int h)
     return n;
 }
 
-// `cols` columns per workgroup (a power of two, log2 = lc).  spec (may be
+// `cols` columns per workgroup (a power of two, log2 = lc).  mean: the numbers
+// subtracted from the rows.  spec (may be
 // NULL): S at [l][m], l = 0 .. L/2.  part[n][l], pitch hp: the sum of S over
 // the modes (+-l, m) of shell n, each m in ascending order with its -m.  LDS:
 // cols (pad(f.m) + 2) elements.  A segment of four columns is 64 bytes of a row
 // of z.
 template <bool kChirp>
 __global__ void __launch_bounds__(1024)
-k_sk_columns(const double2* __restrict__ z, SkFft f, SkTables t, int hc, int lc, double invN,
+k_sk_columns(const double2* __restrict__ z, const double* __restrict__ mean, SkFft f, SkTables t, int hc, int lc,
+             double invN,
              double* __restrict__ spec, double* __restrict__ part, int hp)
 {
     extern __shared__ double2 lds[];
@@ -440,20 +454,23 @@ k_sk_columns(const double2* __restrict__ z, SkFft f, SkTables t, int hc, int lc,
             if (y < n) x[c * lp + pad(y)] = v[b];
         }
         if (l0 == 0) {
-            // Column l = 0 (real parts): the rows' sums, less their mean.
-            double s[kPerThread];
-#pragma unroll
-            for (int b = 0; b < kPerThread; ++b) {
-                const int i = tid + b * T;
-                s[b] = (i & (cols - 1)) == 0 ? v[b].x : 0.0;
-            }
-            double sum[1] = {pairwise(s)};
-            block_sum<1>(sum, red);
-            const double mean = sum[0] / (double)n;
+            // Column l = 0 (real parts): the rows' sums, each the transform's l = 0
+            // and n times what the row's mean differs from theirs.
+            const double m0 = mean[0];
+            double s[kPerThread], m[kPerThread];
 #pragma unroll
             for (int b = 0; b < kPerThread; ++b) {
                 const int i = tid + b * T, y = i >> lc;
-                if ((i & (cols - 1)) == 0 && y < n) x[pad(y)].x = v[b].x - mean;
+                m[b] = (i & (cols - 1)) == 0 && y < n ? mean[y] : m0;
+                s[b] = m[b] - m0;
+            }
+            double sum[1] = {pairwise(s)};
+            block_sum<1>(sum, red);
+            const double centre = m0 + sum[0] / (double)n;
+#pragma unroll
+            for (int b = 0; b < kPerThread; ++b) {
+                const int i = tid + b * T, y = i >> lc;
+                if ((i & (cols - 1)) == 0 && y < n) x[pad(y)].x = v[b].x + (double)n * (m[b] - centre);
             }
         }
     }
@@ -553,9 +570,9 @@ hipError_t passes(const SkPlan& p, const double* rho, double* spec, hipStream_t 
 {
     const SkFft& f = p.fft;
     const int n = f.n, cols = 1 << p.log_cols;
-    hipLaunchKernelGGL(k_sk_rows<kChirp>, dim3((n + 1) / 2), lanes(f.m), sk_lds(f, 1), s, rho, f, p.t, p.hc, p.z);
+    hipLaunchKernelGGL(k_sk_rows<kChirp>, dim3((n + 1) / 2), lanes(f.m), sk_lds(f, 1), s, rho, f, p.t, p.hc, p.z, p.mean);
     hipLaunchKernelGGL(k_sk_columns<kChirp>, dim3((p.hc + cols - 1) / cols), lanes(f.m * cols), sk_lds(f, cols), s,
-                       p.z, f, p.t, p.hc, p.log_cols, 1.0 / ((double)n * (double)n), spec, p.part, p.hp);
+                       p.z, p.mean, f, p.t, p.hc, p.log_cols, 1.0 / ((double)n * (double)n), spec, p.part, p.hp);
     return hipGetLastError();
 }
 
