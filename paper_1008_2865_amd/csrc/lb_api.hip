@@ -1774,9 +1774,13 @@ hipError_t adj_restep(lb_adj* a, int32_t s)
             (e = hipMemcpyAsync(c->buf[0], a->ckpt + (size_t)s * align_up(a->ckpt_bytes), a->ckpt_bytes,
                                 hipMemcpyDeviceToDevice, st)))
             return e;
-        c->cur = 0;
-        c->t = t0;
-        auto work = [&] { return adj_tape_steps(a, n, a->tapes[b], st); };
+        // From the checkpoint each time: adj_replay runs this again where a
+        // capture of it came to nothing.
+        auto work = [&] {
+            c->cur = 0;
+            c->t = t0;
+            return adj_tape_steps(a, n, a->tapes[b], st);
+        };
         if (n == a->every) {
             e = adj_replay(a, a->tape_graphs, b, st, work);
             c->cur = adj_tape_flips(a, n);
