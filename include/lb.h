@@ -80,7 +80,8 @@ typedef struct lb_params {
     int32_t tile_rows;   /* rows a workgroup updates per pipeline stage:
                             0 (library choice), 1 or 2                           */
     int32_t steps_per_launch; /* 0 (library choice: two per launch for LB_F32
-                            and LB_F16DEV on large lattices; with the launch
+                            and LB_F16DEV on large lattices and in tiles of 8
+                            rows or more of the caller's own; with the launch
                             shape left to the library too, up to five per
                             launch on other lattices), 1, or 2: with 2
                             the plain steps of LB_F32 and LB_F16DEV storage

@@ -260,8 +260,10 @@ Geom make_geom2(const lb_params& p, const Geom& g)
 }
 
 // Whether plain steps run two per launch: FP32 or half storage when asked
-// for (steps_per_launch = 2), and by default on lattices of 1.2 million sites
-// large enough for tiles of 8 rows or more.  Below that lb_tile.hip's kernel is
+// for (steps_per_launch = 2), and by default on lattices large enough for tiles of
+// 8 rows or more, if a tile shape is given (512^2 in tiles of 128 x 32: 24.1
+// us/step, one per launch 27.5) or there are 1.2 million sites.  Below that
+// lb_tile.hip's kernel, which chooses its own tiles, is
 // about as fast or faster (us/step against two per launch: 900^2 11.1 and 12.0 in
 // FP32, 12.3 and 12.6 in half storage; 1040^2 13.4 and 13.1, 13.6 and 13.9),
 // above it slower (1120^2 14.5 and 14.2, 15.7 and 14.5; 1140^2 16.1 and 14.2,
@@ -270,7 +272,8 @@ bool use_two(const lb_params& p, const Geom& g2)
 {
     if (p.storage != LB_F32 && p.storage != LB_F16DEV) return false;
     if (p.steps_per_launch == 2) return true;
-    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (int64_t)p.nx * p.ny >= 1200000;
+    const bool shaped = p.tile_x || p.tile_y || p.tile_rows;
+    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (shaped || (int64_t)p.nx * p.ny >= 1200000);
 }
 
 // Tiles of at most w x h sites that cover an nx x ny lattice, rounded up to
