@@ -259,23 +259,6 @@ Geom make_geom2(const lb_params& p, const Geom& g)
     return g2;
 }
 
-// Whether plain steps run two per launch: FP32 or half storage when asked
-// for (steps_per_launch = 2), and by default on lattices large enough for tiles of
-// 8 rows or more, if a tile shape is given (512^2 in tiles of 128 x 32: 24.1
-// us/step, one per launch 27.5) or there are 1.2 million sites.  Below that
-// lb_tile.hip's kernel, which chooses its own tiles, is
-// about as fast or faster (us/step against two per launch: 900^2 11.1 and 12.0 in
-// FP32, 12.3 and 12.6 in half storage; 1040^2 13.4 and 13.1, 13.6 and 13.9),
-// above it slower (1120^2 14.5 and 14.2, 15.7 and 14.5; 1140^2 16.1 and 14.2,
-// 16.3 and 14.5).
-bool use_two(const lb_params& p, const Geom& g2)
-{
-    if (p.storage != LB_F32 && p.storage != LB_F16DEV) return false;
-    if (p.steps_per_launch == 2) return true;
-    const bool shaped = p.tile_x || p.tile_y || p.tile_rows;
-    return p.steps_per_launch == 0 && g2.tile_y >= 8 && (shaped || (int64_t)p.nx * p.ny >= 1200000);
-}
-
 // Tiles of at most w x h sites that cover an nx x ny lattice, rounded up to
 // whole rounds of `slots` resident workgroups.
 int64_t round_tiles(int nx, int ny, int w, int h, int64_t slots)
@@ -356,6 +339,65 @@ bool plane_fits(const lb_params& p, const Geom& g)
     return (uint64_t)g.plane * lbk::storage_bytes(p.storage) < (uint64_t(1) << 32);
 }
 
+// us per step of the row walk at one step per launch, and of the tiles, fitted to
+// 300 lattices and batches.  In both a wave takes about 0.35 ns per row or per
+// site slot in single and 0.6 ns in double precision, once the launch's own time
+// is taken off; a walk's waves also take four rows beyond its tile, and a round of
+// tiles takes all the waves of its workgroups, however few sites they have.  A
+// walk takes at least 0.85 (1.2) us for each row after the second, and neither
+// kernel beats the memory, 4.9 TB/s: 9 values in and 9 out a site, and a part of
+// the halo again, all of it where an XCD's run of the walk's tiles does not reach
+// a tile's vertical neighbour.
+struct WalkCost {
+    bool f64;
+    double waves = 0.0, bytes = 0.0;
+    int rows = 0;
+    explicit WalkCost(int storage) : f64(storage == LB_F64) {}
+    void add(const Geom& g, int storage, bool alone)
+    {
+        waves += (double)g.blocks * (g.tile_x / 64) * (g.tile_y + 4);
+        rows = std::max(rows, g.tile_y);
+        const double again = alone && g.blocks < 16 * g.tiles_x ? 1.0 : 0.35;
+        bytes += 9.0 * (2.0 + again * 4.0 / g.tile_y) * lbk::storage_bytes(storage) * g.nx * (double)g.ny;
+    }
+    double us() const
+    {
+        const double launch = f64 ? 6.0 : 4.0;
+        return std::max({launch + (f64 ? 0.6e-3 : 0.35e-3) * waves, launch + (f64 ? 1.2 : 0.85) * (rows - 2), bytes / 4.9e6});
+    }
+};
+
+// Launches of k steps on `tiles` tiles of at most tx x ty sites.
+double tile_us(int storage, int64_t sites, int64_t tiles, int tx, int ty, int threads, int64_t slots, int k)
+{
+    int64_t site_slots = 0;  // of a thread, over the steps
+    for (int j = 0; j < k; ++j) site_slots += ((tx + 6 * j + 4) * (ty + 6 * j + 4) + threads - 1) / threads;
+    const double round = (storage == LB_F64 ? 0.9 : 0.6) + (storage == LB_F64 ? 0.6e-3 : 0.35e-3) * (double)(site_slots * slots * (threads / 64));
+    const double launch = 3.5 + round * (double)((tiles + slots - 1) / slots);
+    const double halo = (double)((tx + 6 * k - 2) * (ty + 6 * k - 2)) / (tx * ty) - 1.0;
+    const double bytes = 9.0 * (2.0 + 0.5 * halo) * lbk::storage_bytes(storage) * (double)sites;
+    return std::max(launch, bytes / 4.9e6) / k;
+}
+
+// Which launches of up to k steps the tiles take over from the walk: all while one
+// round holds them; else those of several steps unless the estimate is 1.1 times
+// the walk's, and those of one step, which share no launch and no load, where it
+// is 0.95 of it, or 0.8 from 850 000 sites on (FP32 900^2 14.1 on tiles and 15.1 in
+// the walk, 948^2 15.8 and 14.9, 100 x 9000 19.0 and 27.8).  us/step on tiles and in the walk: 60000 x 5 in FP32 27.4 and
+// 11.3, FP64 60000 x 11 40.5 and 30.2, 20000 x 30 in FP32 10.6 and 13.9.
+struct TileUse {
+    int steps = 0;
+    bool single = false;
+    TileUse(int storage, int64_t sites, int64_t tiles, int tx, int ty, const TileClass& c, int k, const WalkCost& walk)
+    {
+        auto gain = [&](int j, double most) {
+            return tiles <= c.slots || tile_us(storage, sites, tiles, tx, ty, c.threads, c.slots, j) <= most * walk.us();
+        };
+        single = gain(1, sites <= 850000 ? 0.95 : 0.8);
+        steps = k > 1 ? (gain(k, 1.1) ? k : 0) : single;
+    }
+};
+
 // Plain steps of several levels per launch (lb_tile.hip), for lattices that
 // do not run two per launch in the row walk.
 struct TilePlan {
@@ -378,13 +420,12 @@ struct TilePlan {
 // workgroups per CU, whose loads overlap each other's arithmetic: 1200^2 24x24
 // (4.9 rounds) 33.4 and 24x26 (4.6) 36.1 against 35.4 for 34x34 tiles, 2048^2
 // 98 against 111 (one step per launch 44 and 128).
-TilePlan make_tile(const lb_params& p, const Geom& g, bool two)
+TilePlan make_tile(const lb_params& p, const Geom& g)
 {
     TilePlan t{};
     const int64_t N = (int64_t)p.nx * p.ny;
-    if (two || p.steps_per_launch != 0 || p.tile_x || p.tile_y || p.tile_rows || !plane_fits(p, g)) return t;
+    if (p.steps_per_launch != 0 || p.tile_x || p.tile_y || p.tile_rows || !plane_fits(p, g)) return t;
     const TileClass c(N, p.storage == LB_F64);
-    t.single = N <= 900000;
     for (int k = c.steps; k >= 1; --k) {
         const int w = std::min(c.width(k), p.nx - 3 * k + 2), h = std::min(c.height(k), p.ny - 3 * k + 2);
         if (w < 4 || h < 4) continue;
@@ -393,11 +434,32 @@ TilePlan make_tile(const lb_params& p, const Geom& g, bool two)
             continue;  // three steps only where they need no more rounds than two
         const TileSplit s = split_tiles(p.nx, p.ny, w, h, 4, c.slots, 6 * k - 2);
         if (!s.tx) continue;
-        t.steps = k;
         t.g = tile_geom(p, g, s.tx, s.ty, c.threads);
+        WalkCost walk(p.storage);
+        walk.add(g, p.storage, true);
+        const TileUse use(p.storage, N, t.g.tiles, s.tx, s.ty, c, k, walk);
+        t.steps = use.steps;
+        t.single = use.single;
         return t;
     }
     return t;
+}
+
+// Whether plain steps run two per launch: FP32 or half storage when asked
+// for (steps_per_launch = 2), and by default on lattices large enough for tiles of
+// 8 rows or more, if a tile shape is given (512^2 in tiles of 128 x 32: 24.1
+// us/step, one per launch 27.5), if the lattice does not run on lb_tile.hip's tiles
+// (100000 x 8: 12.8, on tiles 24.6) or if there are 1.2 million sites.  Below that
+// the tiles are about as fast or faster (us/step against two per launch: 900^2
+// 11.1 and 12.0 in FP32, 12.3 and 12.6 in half storage; 1040^2 13.4 and 13.1, 13.6
+// and 13.9), above it slower (1120^2 14.5 and 14.2, 15.7 and 14.5; 1140^2 16.1 and
+// 14.2, 16.3 and 14.5).
+bool use_two(const lb_params& p, const Geom& g, const Geom& g2)
+{
+    if (p.storage != LB_F32 && p.storage != LB_F16DEV) return false;
+    if (p.steps_per_launch == 2) return true;
+    return p.steps_per_launch == 0 && g2.tile_y >= 8 &&
+           ((int64_t)p.nx * p.ny >= 1200000 || !make_tile(p, g).steps);
 }
 
 // The tile geometry of a launch of `steps` <= t.steps steps.
@@ -601,8 +663,8 @@ int lb_two_step_shape(const lb_params* p, int32_t* tile_x, int32_t* tile_y, int3
 {
     int rc = check_params(p);
     if (rc) return rc;
-    const Geom g2 = make_geom2(*p, make_geom(*p));
-    const bool on = use_two(*p, g2);
+    const Geom g = make_geom(*p), g2 = make_geom2(*p, g);
+    const bool on = use_two(*p, g, g2);
     if (tile_x) *tile_x = on ? g2.tile_x : 0;
     if (tile_y) *tile_y = on ? g2.tile_y : 0;
     if (blocks) *blocks = on ? g2.blocks : 0;
@@ -674,8 +736,8 @@ int lb_init(lb_ctx** out, const lb_params* p, void* workspace, size_t bytes,
     c->p = *p;
     c->g = g;
     c->g2 = make_geom2(*p, g);
-    c->two = use_two(*p, c->g2);
-    c->tile = make_tile(*p, g, c->two);
+    c->two = use_two(*p, g, c->g2);
+    c->tile = c->two ? TilePlan{} : make_tile(*p, g);
     c->coef = make_coef(*p);
     c->device = dev;
     c->stream = st;

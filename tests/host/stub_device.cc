@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 #include <vector>
 
 namespace {
@@ -16,6 +17,7 @@ bool capturing = false;
 int instantiations = 0;
 std::vector<double> levels;
 size_t entry = 0;  // values per tape entry
+std::string route;
 double* at(const void* p) { return static_cast<double*>(const_cast<void*>(p)); }
 }  // namespace
 
@@ -61,11 +63,18 @@ static hipError_t advance(const void* src, void* dst, void* tape, int steps)
 }
 hipError_t launch_tile(int, const void* src, void* dst, const TileGeom& g, const Coef&, void* tape, hipStream_t)
 {
+    route += " t" + std::to_string(g.steps);
     return advance(src, dst, tape, g.steps);
 }
 hipError_t launch_step(int, int mode, const void* src, void* dst, const Geom&, const Coef&, double* tape, hipStream_t)
 {
+    route += " w1";
     return mode == MODE_ENERGY ? hipSuccess : advance(src, dst, mode == MODE_STEP_TAPE ? tape : nullptr, 1);
+}
+hipError_t launch_step2(int, const void* src, void* dst, const Geom&, const Coef&, hipStream_t)
+{
+    route += " w2";
+    return advance(src, dst, nullptr, 2);
 }
 hipError_t launch_final(const double*, int, double t, double, double* row, hipStream_t)
 {
@@ -87,33 +96,70 @@ hipError_t adj_steps(const AdjParams&, const AdjTile& g, const void*, const void
 }
 }  // namespace lbk
 
-int main(int argc, char** argv)
+static int fail()
 {
-    if (argc != 4) return 2;
+    std::fprintf(stderr, "%s\n", lb_last_error());
+    return 1;
+}
+
+static lb_params params(int storage, int nx, int ny)
+{
     lb_params p{};
-    p.nx = p.ny = std::atoi(argv[1]);
-    p.storage = LB_F64;
+    p.nx = nx;
+    p.ny = ny;
+    p.storage = storage;
     p.tau = p.rho0 = 1.0;
     p.G1 = -4.9;
-    const int64_t T = std::atoi(argv[2]);
-    const int32_t every = std::atoi(argv[3]);
+    p.rho_ref = 0.7;
+    return p;
+}
+
+static void* workspace(size_t bytes) { return std::aligned_alloc(256, (bytes + 255) / 256 * 256); }
+
+static int adjoint(int side, int64_t T, int32_t every)
+{
+    const lb_params p = params(LB_F64, side, side);
     entry = (size_t)4 * p.nx * p.ny;
     const size_t bytes = lb_adj_workspace_bytes(&p, T, every);
-    void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    void* ws = workspace(bytes);
     std::memset(ws, 0xff, bytes);
     std::vector<double> rho(entry / 4, 0.7), drho(entry / 4);
     lb_adj* a = nullptr;
     const lb_adj_loss loss{0.0, 0.0, 1e-6};
     double out[4], dG[2];
     if (lb_adj_init(&a, &p, T, every, ws, bytes, reinterpret_cast<void*>(32)) ||
-        lb_adj_forward(a, rho.data(), 0, p.G1, p.G2, &loss, out) || lb_adj_backward(a, dG, drho.data(), 0)) {
-        std::fprintf(stderr, "%s\n", lb_last_error());
-        return 1;
-    }
+        lb_adj_forward(a, rho.data(), 0, p.G1, p.G2, &loss, out) || lb_adj_backward(a, dG, drho.data(), 0))
+        return fail();
     std::printf("%d", instantiations);
     for (double v : levels) std::printf(" %g", v);
     std::printf("\n");
     lb_adj_destroy(a);
     std::free(ws);
     return 0;
+}
+
+static int steps(const lb_params& p, int calls, char** n)
+{
+    const size_t bytes = lb_workspace_bytes(&p);
+    void* ws = workspace(bytes);
+    std::vector<double> rho((size_t)p.nx * p.ny, 0.7);
+    lb_ctx* c = nullptr;
+    if (lb_init(&c, &p, ws, bytes, rho.data(), nullptr, nullptr, 0, nullptr)) return fail();
+    for (int i = 0; i < calls; ++i) {
+        route.clear();
+        if (lb_step(c, std::atoi(n[i]))) return fail();
+        std::printf("%s\n", route.c_str() + 1);
+    }
+    lb_destroy(c);
+    std::free(ws);
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    const std::string mode = argc > 1 ? argv[1] : "";
+    auto arg = [&](int i) { return std::atoi(argv[i]); };
+    if (mode == "adjoint" && argc == 5) return adjoint(arg(2), arg(3), arg(4));
+    if (mode == "steps" && argc > 5) return steps(params(arg(2), arg(3), arg(4)), argc - 5, argv + 5);
+    return 2;
 }
