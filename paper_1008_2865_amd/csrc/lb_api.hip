@@ -382,18 +382,23 @@ double tile_us(int storage, int64_t sites, int64_t tiles, int tx, int ty, int th
 // Which launches of up to k steps the tiles take over from the walk: all while one
 // round holds them; else those of several steps unless the estimate is 1.1 times
 // the walk's, and those of one step, which share no launch and no load, where it
-// is 0.95 of it, or 0.8 from 850 000 sites on (FP32 900^2 14.1 on tiles and 15.1 in
-// the walk, 948^2 15.8 and 14.9, 100 x 9000 19.0 and 27.8).  us/step on tiles and in the walk: 60000 x 5 in FP32 27.4 and
-// 11.3, FP64 60000 x 11 40.5 and 30.2, 20000 x 30 in FP32 10.6 and 13.9.
+// is `one` of it: 0.93 in a batch (FP64 two of 900^2 51 on tiles and 61 in the walk,
+// two of 1200^2 115 and 101, 900 of 32^2 70 and 62), for a lattice 0.95, or 0.85 from
+// 850 000 sites on (FP32 900^2 14.1 and 15.1, 948^2 15.8 and 14.9, 100 x 9000 19.0
+// and 27.8).  us/step of several per launch on tiles and in the walk: 60000 x 5 in
+// FP32 27.4 and 11.3, FP64 60000 x 11 40.5 and 30.2, 20000 x 30 in FP32 10.6 and
+// 13.9; batches in FP32, 1000 lattices of 8^2 26.6 and 12.0, 500 of 16^2 13.9 and
+// 12.2, 300 of 24^2 9.8 and 11.4 (13.7 and 11.3 at one step per call).
 struct TileUse {
     int steps = 0;
     bool single = false;
-    TileUse(int storage, int64_t sites, int64_t tiles, int tx, int ty, const TileClass& c, int k, const WalkCost& walk)
+    TileUse(int storage, int64_t sites, int64_t tiles, int tx, int ty, const TileClass& c, int k, const WalkCost& walk,
+            double one)
     {
         auto gain = [&](int j, double most) {
             return tiles <= c.slots || tile_us(storage, sites, tiles, tx, ty, c.threads, c.slots, j) <= most * walk.us();
         };
-        single = gain(1, sites <= 850000 ? 0.95 : 0.8);
+        single = gain(1, one);
         steps = k > 1 ? (gain(k, 1.1) ? k : 0) : single;
     }
 };
@@ -437,7 +442,7 @@ TilePlan make_tile(const lb_params& p, const Geom& g)
         t.g = tile_geom(p, g, s.tx, s.ty, c.threads);
         WalkCost walk(p.storage);
         walk.add(g, p.storage, true);
-        const TileUse use(p.storage, N, t.g.tiles, s.tx, s.ty, c, k, walk);
+        const TileUse use(p.storage, N, t.g.tiles, s.tx, s.ty, c, k, walk, N <= 850000 ? 0.95 : 0.85);
         t.steps = use.steps;
         t.single = use.single;
         return t;
@@ -538,6 +543,7 @@ struct lb_batch {
     int32_t* tile_lattice2;    // device, two-step tiles (when two)
     lbk::TileBatch tile;       // tiles of several steps per launch
     int tile_steps;            // most of their steps; 0: not used
+    bool tile_single;          // also for one step
     double* partials;          // device, 4 per tile
     int tiles, tiles2;
     bool two;                  // plain steps run two per launch
@@ -1046,6 +1052,7 @@ int check_batch(lb_batch* b)
 // sizes allow, whose count fills no more rounds than the largest would.
 struct BatchTiles {
     int steps, tx, ty, threads, tiles;
+    bool single;  // also for one step
     std::vector<lbk::TileGeom> geom;
 };
 
@@ -1053,10 +1060,13 @@ void batch_tiles(const lb_params* ps, int32_t count, BatchTiles& t)
 {
     int64_t N = 0;
     int least = INT32_MAX;
+    WalkCost walk(ps[0].storage);
     for (int32_t i = 0; i < count; ++i) {
+        const Geom g = make_geom(ps[i]);
         N += (int64_t)ps[i].nx * ps[i].ny;
         least = std::min({least, ps[i].nx, ps[i].ny});
-        if (!plane_fits(ps[i], make_geom(ps[i]))) return;
+        if (!plane_fits(ps[i], g)) return;
+        walk.add(g, ps[i].storage, count == 1);
     }
     const TileClass c(N, ps[0].storage == LB_F64);
     auto tiles = [&](int k, int w, int h) {
@@ -1087,6 +1097,9 @@ void batch_tiles(const lb_params* ps, int32_t count, BatchTiles& t)
             t.tx = std::max(t.tx, t.geom.back().tx);
             t.ty = std::max(t.ty, t.geom.back().ty);
         }
+        const TileUse use(ps[0].storage, N, t.tiles, t.tx, t.ty, c, k, walk, 0.93);
+        if (!use.steps) t = BatchTiles{};
+        t.single = use.single;
         return;
     }
 }
@@ -1255,7 +1268,7 @@ hipError_t batch_run(lb_batch* b, int64_t n, int parity, int64_t t, int64_t* don
         const int k = batch_steps(b, n - *done);
         const int64_t now = t + *done;
         hipError_t e;
-        if (b->tile_steps) {
+        if (b->tile_steps && (k > 1 || b->tile_single)) {
             lbk::TileBatch launch = b->tile;
             launch.parity = parity;
             launch.steps = k;
@@ -1456,6 +1469,7 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     b->tile.threads = L.tile.threads;
     b->tile.tau1 = std::all_of(ps, ps + count, [](const lb_params& p) { return 1.0 / p.tau == 1.0; });
     b->tile_steps = L.tile.steps;
+    b->tile_single = L.tile.single;
     b->partials = reinterpret_cast<double*>(ws + L.partials);
     b->tiles = L.tiles;
     b->tiles2 = L.tiles2;

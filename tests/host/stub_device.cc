@@ -76,6 +76,22 @@ hipError_t launch_step2(int, const void* src, void* dst, const Geom&, const Coef
     route += " w2";
     return advance(src, dst, nullptr, 2);
 }
+hipError_t launch_tile_batch(int, const TileBatch& b, hipStream_t)
+{
+    route += " t" + std::to_string(b.steps);
+    return hipSuccess;
+}
+hipError_t launch_step2_batch(int, bool, int, const BatchLattice*, const int32_t*, int, int, uint32_t, hipStream_t)
+{
+    route += " w2";
+    return hipSuccess;
+}
+hipError_t launch_step_batch(int, int, int, int, int, const BatchLattice*, const int32_t*, int, int, uint32_t, double*, hipStream_t)
+{
+    route += " w1";
+    return hipSuccess;
+}
+void coef_to_f32(const Coef&, float*) {}
 hipError_t launch_final(const double*, int, double t, double, double* row, hipStream_t)
 {
     row[0] = t;
@@ -155,11 +171,31 @@ static int steps(const lb_params& p, int calls, char** n)
     return 0;
 }
 
+static int batch(const lb_params& p, int count, int calls, char** n)
+{
+    const std::vector<lb_params> ps(count, p);
+    const size_t bytes = lb_batch_workspace_bytes(ps.data(), count);
+    void* ws = workspace(bytes);
+    const std::vector<double> rho((size_t)p.nx * p.ny, 0.7);
+    const std::vector<const double*> rhos(count, rho.data());
+    lb_batch* b = nullptr;
+    if (lb_batch_init(&b, ps.data(), count, ws, bytes, rhos.data(), 0, nullptr)) return fail();
+    for (int i = 0; i < calls; ++i) {
+        route.clear();
+        if (lb_batch_step(b, std::atoi(n[i]))) return fail();
+        std::printf("%s\n", route.c_str() + 1);
+    }
+    lb_batch_destroy(b);
+    std::free(ws);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string mode = argc > 1 ? argv[1] : "";
     auto arg = [&](int i) { return std::atoi(argv[i]); };
     if (mode == "adjoint" && argc == 5) return adjoint(arg(2), arg(3), arg(4));
     if (mode == "steps" && argc > 5) return steps(params(arg(2), arg(3), arg(4)), argc - 5, argv + 5);
+    if (mode == "batch" && argc > 6) return batch(params(arg(2), arg(4), arg(5)), arg(3), argc - 6, argv + 6);
     return 2;
 }

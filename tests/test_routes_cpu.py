@@ -49,3 +49,27 @@ def test_lattices_take_the_faster_kernel(program, storage, nx, ny, several, one)
     if storage != B.LB_F64:
         p = B.make_params(nx, ny, storage=storage, rho_ref=0.7)
         assert (B.lb_two_step_shape(p)[0] != 0) == (several == "w2")
+
+
+# (storage, lattices, nx, ny, launches of 6 steps, of 1 step)
+BATCH_ROUTES = [
+    # Many lattices smaller than a tile: 1.1 to 4.4 times the walk's time on tiles.
+    (B.LB_F32, 300, 5, 5, "w1", "w1"), (B.LB_F32, 1000, 8, 8, "w1", "w1"), (B.LB_F64, 3000, 8, 8, "w1", "w1"),
+    (B.LB_F16DEV, 300, 12, 12, "w1", "w1"), (B.LB_F32, 100, 16, 16, "w1", "w1"), (B.LB_F64, 2000, 16, 16, "w1", "w1"),
+    (B.LB_F64, 300, 200, 6, "w1", "w1"),
+    # One step of many rounds.
+    (B.LB_F32, 300, 24, 24, "t3", "w1"), (B.LB_F64, 1400, 24, 24, "t3", "w1"), (B.LB_F64, 2, 1200, 1200, "t2", "w1"),
+    # The tiles keep what they are faster for.
+    (B.LB_F32, 3, 64, 64, "t3", "t1"), (B.LB_F32, 20, 96, 80, "t3", "t1"), (B.LB_F64, 3, 500, 500, "t2", "t1"),
+    (B.LB_F64, 2, 900, 900, "t2", "t1"), (B.LB_F64, 900, 32, 32, "t3", "w1"), (B.LB_F32, 2, 700, 700, "t2", "t1"),
+    (B.LB_F64, 96, 128, 128, "t2", "t1"), (B.LB_F32, 1400, 24, 24, "t3", "t1"),
+    (B.LB_F32, 96, 128, 128, "w2", "w1"), (B.LB_F32, 4, 512, 512, "w2", "w1"),
+]
+
+
+@pytest.mark.parametrize("storage, count, nx, ny, several, one", BATCH_ROUTES)
+def test_batches_take_the_faster_kernel(program, storage, count, nx, ny, several, one):
+    six, single = host.run(program, "batch", storage, count, nx, ny, 6, 1)
+    per = int(several[1])
+    assert six.split() == [several] * (6 // per)
+    assert single == one
