@@ -241,9 +241,11 @@ int lb_batch_two_step_shape(lb_batch* b, int32_t* tile_x, int32_t* tile_y, int32
 
 /* Rows per workgroup of the batch's two-step launches: tile_y in [8, 64], or
  * 0 for the library's choice (the height of least rounds of resident
- * workgroups times rows walked).  Only the launch shape changes: fields stay
- * bit-identical.  Synchronises the stream and drops captured graphs.
- * LB_ERR_STATE if the batch runs one step per launch. */
+ * workgroups times rows walked).  Below a million sites that choice is no
+ * two-step launch; there a batch that fills 1400 workgroups of 16 rows runs two
+ * steps per launch once a height is set.  Only the launch shape changes: fields
+ * stay bit-identical.  Synchronises the stream and drops captured graphs.
+ * LB_ERR_STATE if the batch has no two-step launches. */
 int lb_batch_two_step_tile(lb_batch* b, int32_t tile_y);
 
 /* Context of lattice i, owned by the batch: lb_moments, lb_pseudo_energy,

@@ -547,6 +547,7 @@ struct lb_batch {
     double* partials;          // device, 4 per tile
     int tiles, tiles2;
     bool two;                  // plain steps run two per launch
+    bool two_may;              // or would with a height of the caller's
     bool tau1;                 // tau is 1 in every lattice
     int tile_x2, tile_y2;
     int storage, tile_x, rows_per_iter, min_tile_y;
@@ -1112,7 +1113,8 @@ struct BatchLayout {
     std::vector<size_t> member, member_bytes;
     size_t total;
     int tiles, tiles2, tiles2_cap, tile_y2;
-    bool two;
+    bool two;      // plain steps run two per launch
+    bool two_may;  // or would with a height of the caller's
     std::vector<Geom> geom2;
 };
 
@@ -1199,17 +1201,25 @@ int batch_layout(const lb_params* ps, int32_t count, BatchLayout* L)
     int64_t sites = 0;
     for (int32_t i = 0; i < count; ++i) sites += (int64_t)ps[i].nx * ps[i].ny;
     L->two = (st == LB_F32 || st == LB_F16DEV) && (spl == 2 || (spl == 0 && sites >= 1000000));
-    const int tile_y2 = L->two ? batch_height2(ps, count) : 0;
-    L->tile_y2 = L->two ? tile_y2 : 0;
+    // Batches of many lattices that fill 1400 workgroups of 16 rows take a height
+    // too, and two steps per launch with it, though tiles are faster.
+    L->two_may = L->two;
+    if (spl == 0 && st != LB_F64 && !L->two) {
+        int64_t low = 0;
+        for (int32_t i = 0; i < count; ++i) low += batch_geom2(ps[i], 16).blocks;
+        L->two_may = low >= 1400;
+    }
+    L->tile_y2 = L->two ? batch_height2(ps, count) : 0;
     L->tiles2 = 0;
     L->tiles2_cap = 0;
     L->geom2.assign(count, Geom{});
-    if (L->two)
-        for (int32_t i = 0; i < count; ++i) {
-            L->geom2[i] = batch_geom2(ps[i], tile_y2);
+    for (int32_t i = 0; i < count; ++i) {
+        if (L->two) {
+            L->geom2[i] = batch_geom2(ps[i], L->tile_y2);
             L->tiles2 += L->geom2[i].blocks;
-            L->tiles2_cap += batch_geom2(ps[i], kBatchMinTile2).blocks;
         }
+        if (L->two_may) L->tiles2_cap += batch_geom2(ps[i], kBatchMinTile2).blocks;
+    }
     if ((int64_t)L->tiles2_cap >= (int64_t(1) << 30))
         return fail(LB_ERR_INVALID, "too many two-step tiles in the batch");
     size_t off = 0;
@@ -1474,6 +1484,7 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     b->tiles = L.tiles;
     b->tiles2 = L.tiles2;
     b->two = L.two;
+    b->two_may = L.two_may;
     b->tau1 = b->tile.tau1;
     b->tile_x2 = 128;
     b->tile_y2 = L.tile_y2;
@@ -1573,18 +1584,18 @@ int lb_batch_two_step_tile(lb_batch* b, int32_t tile_y)
 {
     int rc = check_batch(b);
     if (rc) return rc;
-    if (!b->two) return fail(LB_ERR_STATE, "this batch runs one step per launch");
+    if (!b->two_may) return fail(LB_ERR_STATE, "this batch does not run two steps per launch");
     if (tile_y != 0 && (tile_y < kBatchMinTile2 || tile_y > kBatchMaxTile2))
         return fail(LB_ERR_INVALID, "tile_y must be 0 or in [%d, %d] (got %d)", kBatchMinTile2,
                     kBatchMaxTile2, tile_y);
     const int count = (int)b->members.size();
     BatchLayout L;
     if ((rc = batch_layout(b->params.data(), count, &L))) return rc;
-    const int ty = tile_y ? tile_y : L.tile_y2;
+    const int ty = tile_y ? tile_y : L.tile_y2;  // 0: back to the tiles
     std::vector<lbk::BatchLattice> desc = b->host_desc;
     std::vector<int32_t> tl2;
     tl2.reserve(b->tiles2_cap);
-    for (int i = 0; i < count; ++i) {
+    for (int i = 0; ty && i < count; ++i) {
         desc[i].geom2 = batch_geom2(b->params[i], ty);
         desc[i].tile_begin2 = (int32_t)tl2.size();
         tl2.insert(tl2.end(), desc[i].geom2.blocks, i);
@@ -1596,8 +1607,9 @@ int lb_batch_two_step_tile(lb_batch* b, int32_t tile_y)
     hipError_t e = hipStreamSynchronize(b->stream);
     if (!e) e = hipMemcpyAsync(b->desc, desc.data(), sizeof(lbk::BatchLattice) * count,
                                hipMemcpyHostToDevice, b->stream);
-    if (!e) e = hipMemcpyAsync(b->tile_lattice2, tl2.data(), sizeof(int32_t) * tl2.size(),
-                               hipMemcpyHostToDevice, b->stream);
+    if (!e && !tl2.empty())
+        e = hipMemcpyAsync(b->tile_lattice2, tl2.data(), sizeof(int32_t) * tl2.size(),
+                           hipMemcpyHostToDevice, b->stream);
     if (!e) e = hipStreamSynchronize(b->stream);
     if (e) return hip_fail(e, "copy batch tables");
     for (auto& kv : b->graphs) (void)hipGraphExecDestroy(kv.second);
@@ -1605,6 +1617,8 @@ int lb_batch_two_step_tile(lb_batch* b, int32_t tile_y)
     b->host_desc = desc;
     b->tile_y2 = ty;
     b->tiles2 = (int)tl2.size();
+    b->two = ty > 0;
+    b->tile_steps = ty ? 0 : L.tile.steps;
     return LB_OK;
 }
 

@@ -181,6 +181,13 @@ static int batch(const lb_params& p, int count, int calls, char** n)
     lb_batch* b = nullptr;
     if (lb_batch_init(&b, ps.data(), count, ws, bytes, rhos.data(), 0, nullptr)) return fail();
     for (int i = 0; i < calls; ++i) {
+        if (n[i][0] == 'h') {
+            int32_t rows = 0;
+            const int rc = lb_batch_two_step_tile(b, std::atoi(n[i] + 1));
+            lb_batch_two_step_shape(b, nullptr, &rows, nullptr);
+            std::printf("%d %d\n", rc, rows);
+            continue;
+        }
         route.clear();
         if (lb_batch_step(b, std::atoi(n[i]))) return fail();
         std::printf("%s\n", route.c_str() + 1);

@@ -73,3 +73,17 @@ def test_batches_take_the_faster_kernel(program, storage, count, nx, ny, several
     per = int(several[1])
     assert six.split() == [several] * (6 // per)
     assert single == one
+
+
+@pytest.mark.parametrize("storage, count, nx, ny, default", [
+    (B.LB_F32, 467, 40, 48, "t3 t3"), (B.LB_F16DEV, 2000, 16, 16, "t3 t3"), (B.LB_F32, 3000, 8, 8, "w1 w1 w1 w1 w1 w1")])
+def test_many_small_lattices_take_a_two_step_height(program, storage, count, nx, ny, default):
+    # 1400 workgroups of 16 rows and less than a million sites.
+    out = host.run(program, "batch", storage, count, nx, ny, 6, "h16", 6, "h7", "h0", 6)
+    assert out == [default, "0 16", "w2 w2 w2", f"{B.LB_ERR_INVALID} 16", "0 0", default]
+
+
+def test_batches_without_two_step_launches_refuse_a_height(program):
+    for storage, count in ((B.LB_F32, 3), (B.LB_F64, 467)):
+        assert host.run(program, "batch", storage, count, 40, 48, "h16") == [f"{B.LB_ERR_STATE} 0"]
+    assert host.run(program, "batch", B.LB_F32, 4, 512, 512, "h16", 6, "h0", 6)[:2] == ["0 16", "w2 w2 w2"]
