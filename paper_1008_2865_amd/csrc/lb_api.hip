@@ -1,6 +1,7 @@
 // Host side of liblb.so: the C ABI declared in include/lb.h.
 //
-// Validates every argument on the host before any launch, carves the
+// Validates every argument before any launch that uses it (host values here,
+// device values by a copy or a kernel that looks them over), carves the
 // caller's device workspace, keeps the time step, the ping-pong buffer
 // index and the trace bookkeeping, and issues the kernels of
 // lb_kernels.hip on the caller's stream.
@@ -725,14 +726,18 @@ int lb_init(lb_ctx** out, const lb_params* p, void* workspace, size_t bytes,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
     if (inputs_on_device) {
-        int* flag = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.scalars);
-        int bad = 0;
-        if ((e = lbk::launch_clear(flag, st)) || (e = lbk::launch_check(rho_init, N, true, flag, st)) ||
-            (ux_init && (e = lbk::launch_check(ux_init, N, false, flag, st))) ||
-            (uy_init && (e = lbk::launch_check(uy_init, N, false, flag, st))) ||
-            (e = hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, st)) ||
-            (e = hipStreamSynchronize(st)))
-            return hip_fail(e, "check initial fields");
+        // Up to 20 000 sites a copy costs less than the check's launches (64^2 28.6
+        // us for the whole call against 41, 128^2 38.6 and 40.9, 181^2 51.6 and 41.4).
+        int bad = N <= 20000;
+        if (!bad) {
+            int* flag = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.scalars);
+            if ((e = lbk::launch_clear(flag, st)) || (e = lbk::launch_check(rho_init, N, true, flag, st)) ||
+                (ux_init && (e = lbk::launch_check(ux_init, N, false, flag, st))) ||
+                (uy_init && (e = lbk::launch_check(uy_init, N, false, flag, st))) ||
+                (e = hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, st)) ||
+                (e = hipStreamSynchronize(st)))
+                return hip_fail(e, "check initial fields");
+        }
         if (bad && ((rc = field_check_device(rho_init, N, true, "rho_init", st)) ||
                     (ux_init && (rc = field_check_device(ux_init, N, false, "ux_init", st))) ||
                     (uy_init && (rc = field_check_device(uy_init, N, false, "uy_init", st)))))

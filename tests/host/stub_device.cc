@@ -6,6 +6,7 @@
 #include "lb.h"
 #include "lb_internal.h"
 
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -97,7 +98,19 @@ hipError_t launch_final(const double*, int, double t, double, double* row, hipSt
     row[0] = t;
     return hipSuccess;
 }
-hipError_t launch_check(const double*, int64_t, bool, int*, hipStream_t) { return hipSuccess; }
+hipError_t launch_clear(int* flag, hipStream_t)
+{
+    route += " clear";
+    *flag = 0;
+    return hipSuccess;
+}
+hipError_t launch_check(const double* v, int64_t n, bool positive, int* flag, hipStream_t)
+{
+    route += " check";
+    for (int64_t i = 0; i < n; ++i)
+        if (!std::isfinite(v[i]) || (positive && !(v[i] > 0.0))) *flag = 1;
+    return hipSuccess;
+}
 hipError_t adj_tape(int, const void*, const Geom&, const AdjParams&, void*, hipStream_t) { return hipSuccess; }
 hipError_t adj_area(const AdjParams&, const void*, double, void*, double*, hipStream_t) { return hipSuccess; }
 hipError_t adj_seed(const AdjParams&, const void*, const void*, double, double, void*, double*, hipStream_t) { return hipSuccess; }
@@ -197,6 +210,20 @@ static int batch(const lb_params& p, int count, int calls, char** n)
     return 0;
 }
 
+static int init(const lb_params& p, int site, double value)
+{
+    const size_t bytes = lb_workspace_bytes(&p);
+    void* ws = workspace(bytes);
+    std::vector<double> rho((size_t)p.nx * p.ny, 0.7), u(rho.size(), 0.0);
+    rho[site] = value;
+    lb_ctx* c = nullptr;
+    const int rc = lb_init(&c, &p, ws, bytes, rho.data(), u.data(), u.data(), 1, nullptr);
+    std::printf("%d%s\n%s\n", rc, route.c_str(), rc ? lb_last_error() : "");
+    if (!rc) lb_destroy(c);
+    std::free(ws);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string mode = argc > 1 ? argv[1] : "";
@@ -204,5 +231,6 @@ int main(int argc, char** argv)
     if (mode == "adjoint" && argc == 5) return adjoint(arg(2), arg(3), arg(4));
     if (mode == "steps" && argc > 5) return steps(params(arg(2), arg(3), arg(4)), argc - 5, argv + 5);
     if (mode == "batch" && argc > 6) return batch(params(arg(2), arg(4), arg(5)), arg(3), argc - 6, argv + 6);
+    if (mode == "init" && argc == 7) return init(params(arg(2), arg(3), arg(4)), arg(5), std::atof(argv[6]));
     return 2;
 }

@@ -87,3 +87,13 @@ def test_batches_without_two_step_launches_refuse_a_height(program):
     for storage, count in ((B.LB_F32, 3), (B.LB_F64, 467)):
         assert host.run(program, "batch", storage, count, 40, 48, "h16") == [f"{B.LB_ERR_STATE} 0"]
     assert host.run(program, "batch", B.LB_F32, 4, 512, 512, "h16", 6, "h0", 6)[:2] == ["0 16", "w2 w2 w2"]
+
+
+@pytest.mark.parametrize("n, launches", [(5, ""), (64, ""), (141, ""), (142, " clear check check check"),
+                                         (300, " clear check check check")])
+def test_device_fields_are_checked_the_cheaper_way(program, n, launches):
+    # The copy of a small field costs less than three launches and a flag.
+    assert host.run(program, "init", B.LB_F32, n, n, 3, 0.5) == ["0" + launches, ""]
+    for site, value in ((0, "nan"), (n * n - 1, 0.0), (7, -1.0), (11, "inf"), (12, "-inf")):
+        status, message = host.run(program, "init", B.LB_F32, n, n, site, value)
+        assert status == f"{B.LB_ERR_INVALID}{launches}" and f"rho_init[{site}]" in message
