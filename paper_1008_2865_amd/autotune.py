@@ -3,9 +3,10 @@
 Times candidate launch shapes (columns per workgroup, rows per workgroup,
 rows per pipeline stage) on the GPU for a lattice size and storage, and
 caches the fastest in a JSON file (``LB_TUNE_CACHE``, default
-``~/.cache/paper_1008_2865_amd/tiles.json``).  Every candidate runs the
-same library kernels; the tuner only chooses among launch shapes, which do
-not change the computed fields.
+``~/.cache/paper_1008_2865_amd/tiles.json``).  The tuner only chooses among
+launches, which do not change the computed fields; where the library's own
+choice, several steps per launch included, is the fastest, the shape is zeros,
+which leave the launch to the library.
 """
 import json
 import os
@@ -54,7 +55,8 @@ def _save(d):
 def time_shape(nx, ny, storage, tile_x, tile_y, tile_rows, steps=100, warmup=20,
                steps_per_launch=1):
     """Microseconds per step for one launch shape: of the one-step kernel
-    (steps_per_launch = 1), or of the two-step kernel (2; tile_rows unused)."""
+    (steps_per_launch = 1), of the two-step kernel (2; tile_rows unused), or
+    with zeros throughout of the library's choice."""
     import torch
 
     from . import inputs
@@ -77,10 +79,13 @@ def time_shape(nx, ny, storage, tile_x, tile_y, tile_rows, steps=100, warmup=20,
 def tune(nx, ny, storage="f32", candidates=None, refresh=False, steps=100, steps_per_launch=1):
     """Fastest (tile_x, tile_y, tile_rows) for this size and storage: of the
     one-step kernel, or with steps_per_launch = 2 of the two-step kernel
-    (candidates (tile_x, tile_y); tile_rows is returned as 1)."""
+    (candidates (tile_x, tile_y); tile_rows is returned as 1).  Without a
+    candidate list of the caller's the library's own choice is timed too, and
+    (0, 0, 0) returned where it is the fastest."""
     if steps_per_launch == 2:
         return _tune_two_step(nx, ny, storage, candidates, refresh, steps)
-    key = f"{storage}:{nx}x{ny}"
+    # Entries that the library's choice did not take part in stay apart.
+    key = f"{storage}:{nx}x{ny}" if candidates else f"{storage}:{nx}x{ny}:any"
     cache = _load()
     if not refresh and key in cache:
         c = cache[key]
@@ -89,6 +94,8 @@ def tune(nx, ny, storage="f32", candidates=None, refresh=False, steps=100, steps
     if storage == "f64":
         cands = [c for c in cands if c[2] == 1]
     best = None
+    if not candidates:
+        best = (time_shape(nx, ny, storage, 0, 0, 0, steps=steps, steps_per_launch=0), 0, 0, 0)
     for tx, ty, tr in cands:
         if tx > max(64, nx):
             continue
@@ -111,9 +118,9 @@ def _tune_two_step(nx, ny, storage, candidates, refresh, steps):
 
     cands = list(candidates or TWO_STEP_CANDIDATES)
     if candidates is None:
-        dx, dy, _ = B.lb_two_step_shape(B.make_params(nx, ny, storage=STORAGE[storage],
-                                                      rho_ref=1.0))
-        if dx and (dx, dy) not in cands:
+        dx, dy, _ = B.lb_two_step_shape(B.make_params(nx, ny, storage=STORAGE[storage], rho_ref=1.0,
+                                                      steps_per_launch=2))
+        if dx and dy >= 8 and (dx, dy) not in cands:
             cands.append((dx, dy))
     best = None
     for tx, ty in cands:
@@ -130,8 +137,9 @@ def _tune_two_step(nx, ny, storage, candidates, refresh, steps):
 def tune_batch_two_step(batch, heights=BATCH_TWO_STEP_HEIGHTS, refresh=False, steps=20):
     """Set the fastest two-step tile height on a batch that runs plain steps
     two per launch (timed on the batch itself, every lattice in each launch)
-    and return it; 0 when the batch runs one step per launch.  The batch
-    advances while it is timed."""
+    and return it; 0 when the batch runs otherwise.  Without heights of the
+    caller's the library's own is timed too.  The batch advances while it is
+    timed."""
     import hashlib
 
     import torch
@@ -140,6 +148,11 @@ def tune_batch_two_step(batch, heights=BATCH_TWO_STEP_HEIGHTS, refresh=False, st
         return 0
     sig = hashlib.sha1(repr(sorted(batch.shapes)).encode()).hexdigest()[:12]
     key = f"batch-two-step:{batch.storage}:{len(batch.shapes)}:{sig}"
+    if heights is BATCH_TWO_STEP_HEIGHTS:
+        # Entries that the library's height did not take part in stay apart.
+        key += ":any"
+        batch.set_two_step_tile(0)
+        heights = sorted({*BATCH_TWO_STEP_HEIGHTS, batch.two_step_shape()[1]})
     cache = _load()
     if not refresh and key in cache:
         batch.set_two_step_tile(cache[key]["tile_y"])
@@ -168,9 +181,9 @@ def tune_batch(lattices, storage="f32", tile_x=None, tile_ys=(8, 16, 32, 64), ti
     """Shared (tile_x, tile_rows, tile_y) of the one-step kernel for a batch,
     timed on the whole batch at one step per launch (one launch covers every
     lattice, so the batch's own parallelism, not a single lattice's, decides
-    the best tile height).  ``lattices``
-    are LBBatch lattice dicts; tile_x defaults to the widest strip every
-    lattice fills."""
+    the best tile height).  A batch that runs several steps per launch uses it
+    for logged and left-over steps only.  ``lattices`` are LBBatch lattice
+    dicts; tile_x defaults to the widest strip every lattice fills."""
     import hashlib
 
     import torch
