@@ -550,7 +550,7 @@ struct lb_batch {
     bool two;                  // plain steps run two per launch
     bool two_may;              // or would with a height of the caller's
     bool tau1;                 // tau is 1 in every lattice
-    int tile_x2, tile_y2;
+    int tile_y2;
     int storage, tile_x, rows_per_iter, min_tile_y;
     int device;
     hipStream_t stream;
@@ -1128,18 +1128,17 @@ struct BatchLayout {
 constexpr int kBatchMinTile2 = 8;
 constexpr int kBatchMaxTile2 = 64;
 
-// Two-step geometry of a batch member: 128-lane tiles and a tile height
-// shared by the batch.
+// Two-step geometry of a batch member: tiles of kBatchLanes2 lanes and a tile
+// height shared by the batch.
 Geom batch_geom2(const lb_params& p, int tile_y2)
 {
     lb_params q = p;
-    q.tile_x = 128;
+    q.tile_x = lbk::kBatchLanes2;
     q.tile_y = std::min(tile_y2, p.ny);
     return make_geom2(q, make_geom(q));
 }
 
-// Height of the two-step tiles of a batch (128 lanes: the lattices of a batch
-// are narrow).  A workgroup walks its height and 7 rows more; a round of
+// Height of the two-step tiles of a batch.  A workgroup walks its height and 7 rows more; a round of
 // resident workgroups takes about as long per row whether it is full or half
 // empty (single precision, full: 1.1 times).  So the height is the one of least
 // rounds x rows, in single precision up to 48 rows: taller tiles are faster for
@@ -1151,7 +1150,7 @@ Geom batch_geom2(const lb_params& p, int tile_y2)
 // storage 51.0, 38.5.
 int batch_height2(const lb_params* ps, int32_t count)
 {
-    const int64_t slots = step2_slots(ps[0].storage, 128);
+    const int64_t slots = step2_slots(ps[0].storage, lbk::kBatchLanes2);
     const double full = ps[0].storage == LB_F32 ? 1.1 : 1.05;
     const int most = ps[0].storage == LB_F32 ? 48 : kBatchMaxTile2;
     int best = kBatchMinTile2;
@@ -1290,7 +1289,7 @@ hipError_t batch_run(lb_batch* b, int64_t n, int parity, int64_t t, int64_t* don
             launch.step = (uint32_t)now;
             e = lbk::launch_tile_batch(b->storage, launch, b->stream);
         } else if (k == 2) {
-            e = lbk::launch_step2_batch(b->storage, b->tau1, b->tile_x2, b->desc, b->tile_lattice2, b->tiles2, parity,
+            e = lbk::launch_step2_batch(b->storage, b->tau1, b->desc, b->tile_lattice2, b->tiles2, parity,
                                         (uint32_t)now, b->stream);
         } else {
             e = batch_launch(b, lbk::MODE_STEP, parity, now);
@@ -1491,7 +1490,6 @@ int lb_batch_init(lb_batch** out, const lb_params* ps, int32_t count, void* work
     b->two = L.two;
     b->two_may = L.two_may;
     b->tau1 = b->tile.tau1;
-    b->tile_x2 = 128;
     b->tile_y2 = L.tile_y2;
     b->storage = ps[0].storage;
     b->tile_x = c0->g.tile_x;
@@ -1579,7 +1577,7 @@ int lb_batch_two_step_shape(lb_batch* b, int32_t* tile_x, int32_t* tile_y, int32
 {
     int rc = check_batch(b);
     if (rc) return rc;
-    if (tile_x) *tile_x = b->two ? b->tile_x2 : 0;
+    if (tile_x) *tile_x = b->two ? lbk::kBatchLanes2 : 0;
     if (tile_y) *tile_y = b->two ? b->tile_y2 : 0;
     if (blocks) *blocks = b->two ? b->tiles2 : 0;
     return LB_OK;

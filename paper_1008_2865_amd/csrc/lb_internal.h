@@ -113,13 +113,13 @@ hipError_t launch_step(int storage, int mode, const void* src, void* dst,
 hipError_t launch_step2(int storage, const void* src, void* dst, const Geom& g, const Coef& c,
                         hipStream_t s);
 // Two plain steps of every lattice of a batch in one launch (tau1: tau is 1 in
-// every lattice): tiles logical
-// tiles of tile_x lanes, tile_lattice maps each to its lattice, whose geom2
-// gives the tile's place; the launch reads buf[parity] and writes
-// buf[parity ^ 1] of every lattice.
-hipError_t launch_step2_batch(int storage, bool tau1, int tile_x, const BatchLattice* desc,
-                              const int32_t* tile_lattice, int tiles, int parity, uint32_t step,
-                              hipStream_t s);
+// every lattice): tiles logical tiles of kBatchLanes2 lanes (the lattices of a
+// batch are narrow), tile_lattice maps each to its lattice, whose geom2 gives the
+// tile's place; the launch reads buf[parity] and writes buf[parity ^ 1] of every
+// lattice.
+constexpr int kBatchLanes2 = 128;
+hipError_t launch_step2_batch(int storage, bool tau1, const BatchLattice* desc, const int32_t* tile_lattice, int tiles,
+                              int parity, uint32_t step, hipStream_t s);
 // Workgroups of tile_x lanes of the two-step kernel (ST_F32 or ST_F16DEV)
 // resident on the current device at once: the runtime's occupancy for the
 // kernel's registers and LDS, per compute unit, times the compute units.
@@ -185,7 +185,7 @@ hipError_t adj_tape(int storage, const void* buf, const Geom& g, const AdjParams
 // squared, whose halo of 3 steps - 1 sites holds at most as many again.  The
 // tile with 3 steps + 1 sites more on each side wraps around the lattice at
 // most once.
-constexpr int kAdjTileMax = 32, kAdjMaxSteps = 5;
+constexpr int kAdjTileMax = 32, kAdjMaxSteps = 3;
 struct AdjTile {
     int32_t tx, ty, tiles_x, tiles, threads;
     int32_t steps;  // of this launch

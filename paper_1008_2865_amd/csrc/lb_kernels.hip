@@ -997,38 +997,22 @@ hipError_t step2_p(const void* src, void* dst, const Geom& g, const Coef& c, hip
     }
 }
 
-template <class P, bool kTau1>
-hipError_t step2_batch_p(int tile_x, const BatchLattice* desc, const int32_t* tile_lattice,
-                         int tiles, int parity, uint32_t step, hipStream_t s)
+template <class P>
+static hipError_t step2_batch_p(bool tau1, const BatchLattice* desc, const int32_t* tile_lattice, int tiles, int parity,
+                                uint32_t step, hipStream_t s)
 {
-    const dim3 grid(tiles);
-    switch (tile_x) {
-    case 64:
-        hipLaunchKernelGGL((k_step2_batch<P, 64, kTau1>), grid, dim3(64), 0, s, desc, tile_lattice, parity, step);
-        break;
-    case 128:
-        hipLaunchKernelGGL((k_step2_batch<P, 128, kTau1>), grid, dim3(128), 0, s, desc, tile_lattice, parity, step);
-        break;
-    case 256:
-        hipLaunchKernelGGL((k_step2_batch<P, 256, kTau1>), grid, dim3(256), 0, s, desc, tile_lattice, parity, step);
-        break;
-    default: return hipErrorInvalidValue;
-    }
+    const auto kernel = tau1 ? k_step2_batch<P, kBatchLanes2, true> : k_step2_batch<P, kBatchLanes2, false>;
+    hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kBatchLanes2), 0, s, desc, tile_lattice, parity, step);
     return hipGetLastError();
 }
 
-hipError_t launch_step2_batch(int storage, bool tau1, int tile_x, const BatchLattice* desc,
-                              const int32_t* tile_lattice, int tiles, int parity, uint32_t step,
-                              hipStream_t s)
+hipError_t launch_step2_batch(int storage, bool tau1, const BatchLattice* desc, const int32_t* tile_lattice, int tiles,
+                              int parity, uint32_t step, hipStream_t s)
 {
     if (tiles <= 0) return hipErrorInvalidValue;
     switch (storage) {
-    case ST_F32:
-        return tau1 ? step2_batch_p<PF32, true>(tile_x, desc, tile_lattice, tiles, parity, step, s)
-                    : step2_batch_p<PF32, false>(tile_x, desc, tile_lattice, tiles, parity, step, s);
-    case ST_F16DEV:
-        return tau1 ? step2_batch_p<PF16, true>(tile_x, desc, tile_lattice, tiles, parity, step, s)
-                    : step2_batch_p<PF16, false>(tile_x, desc, tile_lattice, tiles, parity, step, s);
+    case ST_F32: return step2_batch_p<PF32>(tau1, desc, tile_lattice, tiles, parity, step, s);
+    case ST_F16DEV: return step2_batch_p<PF16>(tau1, desc, tile_lattice, tiles, parity, step, s);
     default: return hipErrorInvalidValue;
     }
 }

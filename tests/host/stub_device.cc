@@ -82,7 +82,7 @@ hipError_t launch_tile_batch(int, const TileBatch& b, hipStream_t)
     route += " t" + std::to_string(b.steps);
     return hipSuccess;
 }
-hipError_t launch_step2_batch(int, bool, int, const BatchLattice*, const int32_t*, int, int, uint32_t, hipStream_t)
+hipError_t launch_step2_batch(int, bool, const BatchLattice*, const int32_t*, int, int, uint32_t, hipStream_t)
 {
     route += " w2";
     return hipSuccess;
