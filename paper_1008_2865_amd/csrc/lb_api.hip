@@ -1153,11 +1153,13 @@ int batch_height2(const lb_params* ps, int32_t count)
     const int64_t slots = step2_slots(ps[0].storage, lbk::kBatchLanes2);
     const double full = ps[0].storage == LB_F32 ? 1.1 : 1.05;
     const int most = ps[0].storage == LB_F32 ? 48 : kBatchMaxTile2;
+    std::vector<std::pair<int, int>> strips(count);  // a lattice's strips and rows
+    for (int32_t i = 0; i < count; ++i) strips[i] = {batch_geom2(ps[i], kBatchMinTile2).tiles_x, ps[i].ny};
     int best = kBatchMinTile2;
     double least = 0.0;
     for (int h = kBatchMinTile2; h <= most; ++h) {
         int64_t tiles = 0;
-        for (int32_t i = 0; i < count; ++i) tiles += batch_geom2(ps[i], h).blocks;
+        for (const auto& [across, ny] : strips) tiles += (int64_t)across * ((ny + h - 1) / h);
         const int64_t rounds = tiles / slots, rest = tiles % slots;
         const double cost = (h + 7) * (full * (double)rounds +
                                        (rest ? std::max(1.0, full * (double)rest / (double)slots) : 0.0));
