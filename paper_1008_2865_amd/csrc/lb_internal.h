@@ -214,7 +214,8 @@ hipError_t adj_zero(double* p, int64_t n, hipStream_t s);
 
 // Structure factor (lb_structure.hip) of an L x L density field, L <= kSkMaxL.
 constexpr int kSkMaxL = 2048;
-// LDS a workgroup of the column pass may use (160 KB less its static part).
+// LDS a workgroup of the column pass may use (160 KB less its static part; the
+// runtime launches that much without a function's limit being raised).
 constexpr int kSkColumnLds = 159 * 1024;
 // The transform of n points: its passes over m points, m = n or, where n has a
 // prime factor above 7, a smooth m >= 2 n - 1 (by convolution: two transforms

@@ -611,14 +611,6 @@ SkFft sk_fft(int L)
 
 hipError_t sk_prepare(const SkPlan& p, double2* tw, double2* chirp, double2* filter, hipStream_t s)
 {
-    // Four columns of 2048 points take 144 KB of LDS.
-    for (const void* fn : {reinterpret_cast<const void*>(k_sk_columns<false>),
-                           reinterpret_cast<const void*>(k_sk_columns<true>),
-                           reinterpret_cast<const void*>(k_sk_rows<true>),
-                           reinterpret_cast<const void*>(k_sk_chirp)}) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kSkColumnLds);
-        if (e != hipSuccess) return e;
-    }
     const SkFft& f = p.fft;
     hipLaunchKernelGGL(k_sk_twiddles, dim3((f.m + kThreads - 1) / kThreads), dim3(kThreads), 0, s, f.m, tw);
     if (f.chirp)
