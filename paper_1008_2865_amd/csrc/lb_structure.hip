@@ -442,7 +442,17 @@ k_sk_columns(const double2* __restrict__ z, const double* __restrict__ mean, SkF
     const int l0 = group << lc;
     const int nc = min(cols, hc - l0);
     {
+        // Column l = 0 also needs the rows' means: loaded with the rest.
         double2 v[kPerThread];
+        double m[kPerThread] = {}, m0 = 0.0;
+        if (l0 == 0) {
+            m0 = mean[0];
+#pragma unroll
+            for (int b = 0; b < kPerThread; ++b) {
+                const int i = tid + b * T, y = i >> lc;
+                m[b] = mean[(i & (cols - 1)) == 0 && y < n ? y : 0];
+            }
+        }
 #pragma unroll
         for (int b = 0; b < kPerThread; ++b) {
             const int i = tid + b * T, y = i >> lc, c = i & (cols - 1);
@@ -456,14 +466,9 @@ k_sk_columns(const double2* __restrict__ z, const double* __restrict__ mean, SkF
         if (l0 == 0) {
             // Column l = 0 (real parts): the rows' sums, each the transform's l = 0
             // and n times what the row's mean differs from theirs.
-            const double m0 = mean[0];
-            double s[kPerThread], m[kPerThread];
+            double s[kPerThread];
 #pragma unroll
-            for (int b = 0; b < kPerThread; ++b) {
-                const int i = tid + b * T, y = i >> lc;
-                m[b] = (i & (cols - 1)) == 0 && y < n ? mean[y] : m0;
-                s[b] = m[b] - m0;
-            }
+            for (int b = 0; b < kPerThread; ++b) s[b] = m[b] - m0;
             double sum[1] = {pairwise(s)};
             block_sum<1>(sum, red);
             const double centre = m0 + sum[0] / (double)n;
