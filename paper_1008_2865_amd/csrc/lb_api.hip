@@ -189,16 +189,17 @@ int64_t step2_slots(int storage, int tile_x)
 //   - half storage, whose two-step kernel is not bound by memory: the
 //     tallest 256-lane tiles of at most 128 rows whose last round is full.
 // Measured on MI355X (FP32, us/step; one step per launch in brackets):
-//   1200^2 128x8 18.0 (20.0);  1800^2 128x18 30.0, 128x24 33.3 (43.0);
-//   2048^2 128x23 41.4, 128x24 42.1 (61.2);  2500^2 128x48 66.2, 128x40
-//   66.7 (115.7);  3000^2 256x47 81.3, 256x48 83.0, 128x48 108.6 (151.9);
-//   4096^2 256x92 144.0, 128x92 146.2, 256x46 147.5 (243.9);  5120^2
-//   256x47 227.7, 256x71 231.5, 256x143 233.7;  8192^2 256x45 589.6,
-//   256x48 604.6, 256x90 601.6, 256x179 619.7, 128x48 658.4 (1037.9).
-// Half storage, us per launch: 8192^2 256x119 840-848 (three rounds),
-// 256x90 847, 256x179 850, 256x357 860, 256x56 857-872 (6.3 rounds),
-// 256x104 883 (3.4 rounds), 256x164 907 (2.1 rounds); 4096^2 256x92 235,
-// 256x46 241-243, 256x56 248.
+//   1200^2 128x8 14.1 (19.6);  1800^2 128x18 23.9, 128x24 24.4 (42.6);
+//   2048^2 128x23 38.5, 128x24 39.2, 256x46 45.2 (57.6);  2500^2 128x35 54.0,
+//   128x40 55.1, 128x48 56.1 (115);  3000^2 256x47 72.4, 256x48 68.8, 128x48
+//   94.1 (152);  3500^2 256x65 108, 256x47 131 (203);  4096^2 256x92 137,
+//   128x92 131, 256x46 138 (245);  5120^2 256x47 225, 256x71 228, 256x143 227
+//   (390);  6144^2 256x51 320, 256x48 337 (549);  8192^2 256x45 587, 256x48
+//   606, 256x90 594, 256x179 576, 128x48 609 (1037).
+// Half storage: 4096^2 256x92 98, 256x46 105, 256x56 113 (142);  6144^2 256x101
+//   217, 256x48 238 (306);  8192^2 256x119 381 (three rounds), 256x90 388,
+//   256x179 377, 256x357 370, 256x56 404 (6.3 rounds), 256x104 405 (3.4),
+//   256x164 423 (2.1) (568).
 Geom make_geom2(const lb_params& p, const Geom& g)
 {
     Geom g2 = g;
@@ -1138,16 +1139,19 @@ Geom batch_geom2(const lb_params& p, int tile_y2)
     return make_geom2(q, make_geom(q));
 }
 
-// Height of the two-step tiles of a batch.  A workgroup walks its height and 7 rows more; a round of
-// resident workgroups takes about as long per row whether it is full or half
-// empty (single precision, full: 1.1 times).  So the height is the one of least
-// rounds x rows, in single precision up to 48 rows: taller tiles are faster for
-// a batch alone, slower for several at once.  Measured us/step, 20 lattices of
-// 9.2 million sites, FP32 (alone; three batches on three streams): 48 rows (1776
-// workgroups, 1.2 rounds of 1536) 106, 81.9; 28 (2.0) 91.0, 81.2; 60 (0.95) 85.0,
-// 83.6; 20 (2.8) 94.8, 82.6; half storage 48 88.8, 58.9, 28 69.2, 62.7, 60 64.9,
-// 57.8.  13 lattices of 4.9 million alone: FP32 24 (1.2) 57.8, 32 (0.9) 47.1; half
-// storage 51.0, 38.5.
+// Height of the two-step tiles of a batch.  A workgroup walks its height and 7
+// rows more; a round of resident workgroups takes about as long per row whether
+// it is full or half empty (full: 1.1 times in single precision, 1.05 in half
+// storage).  So the height is the one of least rounds x rows: the model ranks
+// heights as measured, though their times differ by less than half of what it
+// says, for the memory's share.  In single precision up to 48 rows: taller tiles
+// are faster for a batch alone, slower for several at once.  Measured us/step
+// (alone; three batches on three streams): 20 lattices of 9.1 million sites in
+// FP32 16 rows (3.3 rounds of 1536) 101, 89.2; 20 (2.7) 97.0, 86.7; 28 (1.9) 94.1,
+// 85.5; 48 (1.1) 110, 86.0; 56 (0.98) 86.4, 87.2; 64 (0.86) 90.6, 86.8; half storage
+// 28 68.6, 65.6; 48 88.8, 62.6; 56 62.5, 61.4; 64 68.5, 60.8.  13 lattices of 4.8
+// million: FP32 24 (1.1) 58.0, 44.4; 28 (0.96) 45.1, 44.6; 48 50.7, 44.7; half
+// storage 51.5, 35.8; 36.3, 34.0; 44.8, 32.9.
 int batch_height2(const lb_params* ps, int32_t count)
 {
     const int64_t slots = step2_slots(ps[0].storage, lbk::kBatchLanes2);
@@ -2281,7 +2285,8 @@ SkLayout sk_layout(int32_t L)
     S.part = off; off += align_up((size_t)S.nshell * S.hp * sizeof(double));
     S.count = off; off += align_up((size_t)S.nshell * sizeof(double));
     S.rho = off; off += align_up((size_t)N * sizeof(double));
-    // The size callers have been asked for: 52 bytes per mode.
+    // At least 52 bytes per mode, what a full complex transform took (a host test
+    // holds the size above 40); the regions take 23.
     S.total = std::max(off, align_up((size_t)N * 52));
     return S;
 }

@@ -1,10 +1,11 @@
 // HIP kernels of the two-belt Shan-Chen lattice Boltzmann step for gfx950.
 //
-// Plain steps run several per launch: on large lattices two in k_step2 below,
-// else in the tiles of lb_tile.hip.  k_step runs the logged steps, the steps
-// left over and those asked for one per launch or with a tile shape of their
-// own.  It performs one full time step of eq. (1) of the paper for a strip of
-// the lattice in a single pass over HBM:
+// Plain steps run several per launch: on large lattices and in tiles of the
+// caller's own two in k_step2 below, else in the tiles of lb_tile.hip.  k_step
+// runs the logged steps, the steps left over, those asked for one per launch,
+// tiles of the caller's own in double precision, and lattices whose tiles would
+// hold few sites.  It performs one full time step of eq. (1) of the paper for a
+// strip of the lattice in a single pass over HBM:
 //   pull-stream (read each population once from its upstream site),
 //   moments, psi(rho), the 24-link two-belt force of eq. (FORCE),
 //   BGK collision at the force-shifted velocity, and a coalesced store.

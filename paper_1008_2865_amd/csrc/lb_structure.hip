@@ -22,9 +22,9 @@
 // rate.  The passes move 33.5 MB of density, 33.6 MB of row spectra out and
 // in again, and 2 x 6 MB of run sums, where a full complex transform with a
 // transpose and a gather of every mode into its shell moved 386 MB.  A whole
-// evaluation on MI355X: 2048^2 238 -> 70 us, 1000^2 (radices 8, 5, 5, 5 in
-// place of the direct sum) 1418 -> 51, 521^2 (by convolution) 346 -> 60, 2039^2
-// 9424 -> 152, 512^2 41, 40^2 74 -> 31.
+// evaluation on MI355X: 2048^2 235 -> 71.5 us, 1000^2 (radices 8, 5, 5, 5 in
+// place of the direct sum) 1407 -> 51, 521^2 (by convolution) 347 -> 59, 2039^2
+// 9339 -> 160, 512^2 82 -> 40, 40^2 71 -> 29.
 #include "lb_internal.h"
 
 #include <hip/hip_runtime.h>
