@@ -301,7 +301,8 @@ k_sk_chirp(SkFft f, const double2* __restrict__ tw, double2* __restrict__ chirp,
 }
 
 // Fixed-order workgroup sum of NV values per thread; every thread receives
-// the results.  red holds NV x waves doubles (at most 16 waves).
+// the results.  red holds NV x waves doubles (at most 16 waves) and serves one
+// sum: nothing waits for its readers.
 template <int NV>
 __device__ __forceinline__ void block_sum(double (&v)[NV], double* red)
 {
@@ -324,7 +325,6 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* red)
             for (int w = 0; w < h; ++w) t[w] += t[w + h];
         v[q] = t[0];
     }
-    __syncthreads();
 }
 
 // Sum of kPerThread values, pairwise.
