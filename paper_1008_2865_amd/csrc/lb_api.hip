@@ -342,7 +342,7 @@ bool plane_fits(const lb_params& p, const Geom& g)
 }
 
 // us per step of the row walk at one step per launch, and of the tiles, fitted to
-// 300 lattices and batches.  In both a wave takes about 0.35 ns per row or per
+// 488 timings of lattices and batches.  In both a wave takes about 0.35 ns per row or per
 // site slot in single and 0.6 ns in double precision, once the launch's own time
 // is taken off; a walk's waves also take four rows beyond its tile, and a round of
 // tiles takes all the waves of its workgroups, however few sites they have.  A
